@@ -8,10 +8,9 @@ namespace mbpt {
 
 // Dynamic LDS of a sample kernel; ntab = HF spline tables held (0, 1 or 2).
 size_t sample_lds_bytes(int nd, int nb, int block, int ntab);
+// Items [olist[k0].x, olist[k0].x + nitems) of the tasks listed in olist[k0, k1),
+// or with k1 < 0 the nitems items of task k0.
 // group: tasks of several descriptors may be present (diagram groups).
-hipError_t launch_sample_single(const KArgs &a, int task, int order, int q, int prec, bool group,
-                                int nitems, int block, hipStream_t st);
-// Items [olist[k0].x, olist[k0].x + nitems) of the tasks listed in olist[k0, k1).
 hipError_t launch_sample_order(const KArgs &a, int order, int q, int prec, bool group, int k0,
                                int k1, int nitems, int block, hipStream_t st);
 // The same items with a persistent grid (about as many blocks as are resident
@@ -19,12 +18,6 @@ hipError_t launch_sample_order(const KArgs &a, int order, int q, int prec, bool 
 // counter a.queue[order] (zero at launch).
 hipError_t launch_sample_persistent(const KArgs &a, int order, int q, int prec, bool group, int k0,
                                     int k1, int nitems, int block, int cus, hipStream_t st);
-// Items of the tasks of the fourth-order diagram `id` (olist[k0, k1), nitems
-// items from olist[k0].x) in nuclear matter with the quartic regulator and the
-// polynomial label sums, fp64 (prec 0) or fp32 (1): the per-diagram kernel
-// with compile-time descriptor masks (kernels_o4fixed.hip).
-hipError_t launch_sample_order_fixed4(const KArgs &a, int id, int prec, int k0, int k1, int nitems,
-                                      int block, hipStream_t st);
 // Iteration end of tasks [first_task, first_task + ntasks) that take part in
 // iteration step_iter of the current launch sequence (plan > step_iter).
 hipError_t launch_finish(const KArgs &a, int first_task, int ntasks, int step_iter, double alpha,
@@ -46,9 +39,6 @@ hipError_t launch_hf(const KArgs &a, const double *gl, int first, int ntasks, in
 
 // Per-(order, q) launchers, defined in kernels_inst.hip (one object per pair).
 template <int ORDER, int Q>
-hipError_t launch_single_oq(const KArgs &a, int t, int prec, bool group, int nitems, int block,
-                            hipStream_t st);
-template <int ORDER, int Q>
 hipError_t launch_order_oq(const KArgs &a, int prec, bool group, int k0, int k1, int grid,
                            int block, hipStream_t st);
 template <int ORDER, int Q>
@@ -58,23 +48,15 @@ template <int ORDER, int Q>
 hipError_t launch_dump_oq(const KArgs &a, int t, int prec, bool group, uint32_t iter,
                           uint64_t first, uint64_t count, double *out, double *out_reg,
                           hipStream_t st);
-// Per-diagram fourth-order launchers for the ids [FIRST, FIRST + kFixed4Chunk),
-// one translation unit each.
-constexpr int kFixed4Chunk = 10;
-template <int FIRST>
-hipError_t launch_o4_fixed(const KArgs &a, int id, int prec, int k0, int k1, int nitems, int block,
-                           hipStream_t st);
+// The fourth-order nuclear-matter kernels with compile-time diagrams (fixed4),
+// one translation unit per precision (kernels_o4fixed.hip).
+template <int P>
+hipError_t launch_o4_fixed(const KArgs &a, int k0, int k1, int grid, int block, hipStream_t st);
 template <>
-hipError_t launch_o4_fixed<0>(const KArgs &, int, int, int, int, int, int, hipStream_t);
+hipError_t launch_o4_fixed<0>(const KArgs &, int, int, int, int, hipStream_t);
 template <>
-hipError_t launch_o4_fixed<10>(const KArgs &, int, int, int, int, int, int, hipStream_t);
-template <>
-hipError_t launch_o4_fixed<20>(const KArgs &, int, int, int, int, int, int, hipStream_t);
-template <>
-hipError_t launch_o4_fixed<30>(const KArgs &, int, int, int, int, int, int, hipStream_t);
+hipError_t launch_o4_fixed<1>(const KArgs &, int, int, int, int, hipStream_t);
 #define MBPT_DECLARE_OQ(O, Q)                                                                   \
-  template <>                                                                                   \
-  hipError_t launch_single_oq<O, Q>(const KArgs &, int, int, bool, int, int, hipStream_t);      \
   template <>                                                                                   \
   hipError_t launch_order_oq<O, Q>(const KArgs &, int, bool, int, int, int, int, hipStream_t);  \
   template <>                                                                                   \

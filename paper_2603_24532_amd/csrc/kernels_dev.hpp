@@ -80,10 +80,21 @@ struct SampleLds {
   const void *cyc;  // label-cycle table(s) of the item's diagram(s) (cycle-form kernels)
 };
 
-// Diagram variant of a sample kernel's work items (template argument VF):
-// a diagram id >= 0 fixes the descriptor masks at compile time (per-diagram
-// kernels); kPerItem picks the variant per work item (with_variant).
-constexpr int kPerItem = -2;
+// Fourth-order nuclear-matter single diagrams with the free spectrum, the
+// quartic regulator and the polynomial label sums: the sample kernels branch
+// per work item to code with the diagram's masks and label cycles as
+// compile-time constants (all 39 diagrams in one kernel, see with_variant).
+// One launch covers every diagram, so its last, partly filled round of blocks
+// is paid once per iteration: 39 launches, one per diagram, left the device
+// idle at the end of each.  585 tasks, MI355X: 2^21 samples fp32 34.3 -> 24.8
+// ms per iteration, 500 009 samples fp64 21.3 -> 7.1 ms; one task per launch
+// (2^18 samples, fp32) 52 -> 45 us per iteration against the
+// descriptor-driven code.
+constexpr int kFixed4Diagrams = 39;
+template <int ORDER, int Q, int P, bool X, int HE>
+constexpr bool fixed4() {
+  return ORDER == 4 && Q == 4 && (P == 0 || P == 1) && !X && HE == 2;
+}
 
 // The descriptor-driven single-diagram sample kernels of orders 4 and 5 read
 // the loop coefficients of their momentum sums decoded in the descriptor
@@ -93,9 +104,9 @@ constexpr int kPerItem = -2;
 // faster at fourth order (per task, with components, neutron matter), 6-10%
 // at fifth order, and 5-10% in the persistent kernels; against a table of
 // the same values in LDS, 2-9% faster.
-template <int ORDER, int P, int VF>
+template <int ORDER, int P>
 constexpr bool desc_coef() {
-  return ORDER >= 4 && !(P == 3 || P == 4 || P == 6) && VF < 0;  // not the group modes
+  return ORDER >= 4 && !(P == 3 || P == 4 || P == 6);  // not the group modes
 }
 
 // Label-cycle bit vectors: bit k of CycWord<ORDER> stands for cycle k of a
@@ -335,9 +346,14 @@ __device__ __forceinline__ bool loop_part_of(const DiagDev *__restrict__ D, int 
 // whose first descriptor is D: the one diagram of orders 1-2 (also as a
 // single-member group), the diagram id at order 3 for single-diagram tasks,
 // for the cycle form (CYF) at fifth order kNarrowCycles where the diagram
-// has at most kNarrowCycleMax cycles, the generic path (-1) otherwise.  The
-// branch is uniform per work item.
-template <int ORDER, bool G, bool CYF = false, typename Fn>
+// has at most kNarrowCycleMax cycles, the diagram id at order 4 where the
+// kernel holds them all (FX4, see fixed4), the generic path (-1) otherwise.
+// The branch is uniform per work item.
+template <typename Fn, int... I>
+__device__ __forceinline__ void with_id(std::integer_sequence<int, I...>, int id, Fn &&f) {
+  (void)((id == I ? (f(std::integral_constant<int, I>{}), true) : false) || ...);
+}
+template <int ORDER, bool G, bool CYF = false, bool FX4 = false, typename Fn>
 __device__ __forceinline__ void with_variant(const DiagDev *__restrict__ D, Fn &&f) {
   if constexpr (ORDER <= 2) {
     f(std::integral_constant<int, 0>{});
@@ -346,6 +362,8 @@ __device__ __forceinline__ void with_variant(const DiagDev *__restrict__ D, Fn &
     if (D->id == 0) f(std::integral_constant<int, 0>{});
     else if (D->id == 1) f(std::integral_constant<int, 1>{});
     else f(std::integral_constant<int, 2>{});
+  } else if constexpr (FX4) {
+    with_id(std::make_integer_sequence<int, kFixed4Diagrams>{}, D->id, f);
   } else if constexpr (ORDER >= 5 && CYF) {
     if (D->ncyc <= kNarrowCycleMax) f(std::integral_constant<int, kNarrowCycles>{});
     else f(std::integral_constant<int, -1>{});
@@ -1513,8 +1531,8 @@ __device__ __forceinline__ void hist_flush(const KArgs &a, int t, const double *
 
 // The samples of one work item of task t (the task's tables in LDS): sums,
 // histogram entries (LDS), and the item's partial sums and counters.
-// VF: the diagram variant (see kPerItem).
-template <int ORDER, int Q, int P, bool X, int HE, int VF = kPerItem>
+// FX4: the code of each fourth-order diagram (see fixed4).
+template <int ORDER, int Q, int P, bool X, int HE, bool FX4 = false>
 __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, const BlockLds &B) {
   constexpr int ND = 3 * (ORDER + 1);
   const TaskDev *__restrict__ T = a.tasks + t;
@@ -1566,10 +1584,8 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
   // the sample loops, specialised per diagram variant (uniform per item)
   auto loops = [&](auto vt) {
     constexpr int V = decltype(vt)::value;
-    // loop coefficients from the LDS table (descriptor-driven kernels of
-    // orders 4 and 5)
     // the loop coefficients decoded in the descriptor (desc_coef)
-    constexpr bool TD = desc_coef<ORDER, P, VF>() && !FixedMasks<ORDER, V>::kFixed;
+    constexpr bool TD = desc_coef<ORDER, P>() && !FixedMasks<ORDER, V>::kFixed;
     const double jc = jac_const<ORDER, V>(a, T, D);
     if constexpr (SCR && PP == 0) {
       int pn = 0;  // wave-uniform
@@ -1703,8 +1719,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
       while (qn > 0) drain(qn < 64 ? qn : 64);
     }
   };
-  if constexpr (VF >= 0) loops(std::integral_constant<int, VF>{});
-  else with_variant<ORDER, G, cycle_form<ORDER, Q, G, X, PP == 2>()>(D, loops);
+  with_variant<ORDER, G, cycle_form<ORDER, Q, G, X, PP == 2>(), FX4>(D, loops);
   // wavefront butterfly, then waves in order (compensated pairs s + c)
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
@@ -1772,13 +1787,13 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
 }
 
 // One work item with its own setup and histogram merge.
-template <int ORDER, int Q, int P, bool X, int HE, int VF = kPerItem>
+template <int ORDER, int Q, int P, bool X, int HE>
 __device__ __forceinline__ void process_item(const KArgs &a, int t, int item, double *smem) {
   BlockLds B;
   block_lds<ORDER, Q, P, X>(a, smem, B);
   task_lds<ORDER, Q, P, X>(a, t, B);
   __syncthreads();
-  item_samples<ORDER, Q, P, X, HE, VF>(a, t, item, B);
+  item_samples<ORDER, Q, P, X, HE, fixed4<ORDER, Q, P, X, HE>()>(a, t, item, B);
   __syncthreads();
   hist_flush<ORDER>(a, t, B.h);
 }
@@ -1806,8 +1821,9 @@ __device__ __forceinline__ void process_item(const KArgs &a, int t, int item, do
 // - fifth-order nuclear matter with the Pauli screen: fp32 at 3 waves beats 4
 //   by 8% and 2 by 11%, fp64 at 3 beats 2 by 11% and 4 by 16%.
 // Other kernels fit their natural occupancy.
-template <int ORDER, int Q, int P, bool X>
+template <int ORDER, int Q, int P, bool X, int HE>
 constexpr int min_waves() {
+  if (fixed4<ORDER, Q, P, X, HE>()) return 3;
   if (P == 2) {
     if (ORDER == 2) return 3;
     if (ORDER == 3 || ORDER == 4) return 2;
@@ -1840,60 +1856,33 @@ constexpr int persistent_waves() {
     if (ORDER == 4) return P == 1 ? 3 : 2;
     if (ORDER == 5) return 2;
   }
-  return min_waves<ORDER, Q, P, X>();
+  return min_waves<ORDER, Q, P, X, 0>();
 }
 
-// One task per launch: block b processes work item item_begin + b.
+// One launch over work items, one block per item.  k1 > k0: the items of the
+// tasks of one order; olist[k0, k1) lists them as (first item, task) with
+// ascending first item, their items are numbered contiguously from olist[k0].x,
+// and block b takes item olist[k0].x + b.  One launch per order keeps each
+// launch's register allocation that of its own order.  k1 < 0: the items of
+// task k0 alone.
 template <int ORDER, int Q, int P, bool X, int HE>
-__global__ __launch_bounds__(256, (min_waves<ORDER, Q, P, X>())) void sample_single(KArgs a, int t) {
+__global__ __launch_bounds__(256, (min_waves<ORDER, Q, P, X, HE>())) void sample_order(KArgs a, int k0, int k1) {
   extern __shared__ double smem[];
-  process_item<ORDER, Q, P, X, HE>(a, t, a.tasks[t].item_begin + blockIdx.x, smem);
-}
-
-// One launch over the work items of the tasks of one order: olist[k0, k1)
-// lists them as (first item, task) with ascending first item, their items are
-// numbered contiguously from olist[k0].x, and block b takes item
-// olist[k0].x + b.  One launch per order keeps each launch's register
-// allocation that of its own order.
-template <int ORDER, int Q, int P, bool X, int HE>
-__global__ __launch_bounds__(256, (min_waves<ORDER, Q, P, X>())) void sample_order(KArgs a, int k0, int k1) {
-  extern __shared__ double smem[];
-  const int2 *__restrict__ ol = a.olist;
-  const int item = ol[k0].x + static_cast<int>(blockIdx.x);
-  int lo = k0, hi = k1 - 1;  // last entry with first item <= item
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (ol[mid].x <= item) lo = mid;
-    else hi = mid - 1;
+  int t = k0, item;
+  if (k1 < 0) {
+    item = a.tasks[t].item_begin + static_cast<int>(blockIdx.x);
+  } else {
+    const int2 *__restrict__ ol = a.olist;
+    item = ol[k0].x + static_cast<int>(blockIdx.x);
+    int lo = k0, hi = k1 - 1;  // last entry with first item <= item
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (ol[mid].x <= item) lo = mid;
+      else hi = mid - 1;
+    }
+    t = ol[lo].y;
   }
-  process_item<ORDER, Q, P, X, HE>(a, ol[lo].y, item, smem);
-}
-
-// sample_order for the tasks of one diagram whose descriptor masks and label
-// cycles are compile-time constants (FixedMasks<ORDER, V>, V = the diagram
-// id): the loop-momentum sums keep only their nonzero terms and need no
-// scalar decoding, and the cycle words take no scalar registers.  The same
-// operations as the descriptor-driven kernel (a product with a coefficient 0,
-// +-1, +-2 or +-1/2 is exact), but with the masks known the compiler may fuse
-// other multiply-adds (shared vertex momenta), so the weights agree to their
-// last bits.  Built for 3 waves per SIMD, as measured on the 585
-// fourth-order nuclear-matter tasks: fp64 44.1 Gevals/s at 3 against 36.6 at
-// 4 and 44.1 at 2; fp32 47.6 at 3 against 41.0 at 2 and 49.5 at 4, where 31
-// spilled VGPRs raise the HBM traffic from 1.1 GB to 17 GB per iteration.
-template <int ORDER, int Q, int P, int HE, int V>
-__global__ __launch_bounds__(256, 3) void sample_order_fixed(
-    KArgs a, int k0, int k1) {
-  static_assert(FixedMasks<ORDER, V>::kFixed, "a per-diagram kernel needs the diagram's masks");
-  extern __shared__ double smem[];
-  const int2 *__restrict__ ol = a.olist;
-  const int item = ol[k0].x + static_cast<int>(blockIdx.x);
-  int lo = k0, hi = k1 - 1;  // last entry with first item <= item
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (ol[mid].x <= item) lo = mid;
-    else hi = mid - 1;
-  }
-  process_item<ORDER, Q, P, false, HE, V>(a, ol[lo].y, item, smem);
+  process_item<ORDER, Q, P, X, HE>(a, t, item, smem);
 }
 
 // Persistent launch over the work items of the tasks of one order (as

@@ -48,31 +48,21 @@ hipError_t with_kernel(const KArgs &a, int m, Fn &&fn) {
 }  // namespace
 
 template <>
-hipError_t launch_single_oq<O, Q>(const KArgs &a, int t, int prec, bool group, int nitems,
-                                  int block, hipStream_t st) {
-  return with_kernel(a, mode_of(a, prec, group), [&](auto p, auto x, auto h) -> hipError_t {
-    constexpr int P = decltype(p)::value;
-    constexpr bool X = decltype(x)::value;
-    constexpr int HE = decltype(h)::value;
-    const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
-                       cycle_lds_bytes<O, Q, P, X>();
-    hipLaunchKernelGGL((sample_single<O, Q, P, X, HE>), dim3(nitems), dim3(block), lds, st, a, t);
-    return hipGetLastError();
-  });
-}
-
-template <>
 hipError_t launch_order_oq<O, Q>(const KArgs &a, int prec, bool group, int k0, int k1, int grid,
                                  int block, hipStream_t st) {
   return with_kernel(a, mode_of(a, prec, group), [&](auto p, auto x, auto h) -> hipError_t {
     constexpr int P = decltype(p)::value;
     constexpr bool X = decltype(x)::value;
     constexpr int HE = decltype(h)::value;
-    const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
-                       cycle_lds_bytes<O, Q, P, X>();
-    hipLaunchKernelGGL((sample_order<O, Q, P, X, HE>), dim3(grid), dim3(block), lds, st, a, k0,
-                       k1);
-    return hipGetLastError();
+    if constexpr (fixed4<O, Q, P, X, HE>()) {
+      return launch_o4_fixed<P>(a, k0, k1, grid, block, st);
+    } else {
+      const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
+                         cycle_lds_bytes<O, Q, P, X>();
+      hipLaunchKernelGGL((sample_order<O, Q, P, X, HE>), dim3(grid), dim3(block), lds, st, a, k0,
+                         k1);
+      return hipGetLastError();
+    }
   });
 }
 

@@ -1194,9 +1194,9 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
       for (int t = 0; t < nt; ++t) {
         size_t slot = 0;
         if (timed) timed_begin(ctx, slot);
-        HIPCHK(ctx, launch_sample_single(a, t, set->tasks[t].order, set->q, ctx->desc.precision,
-                                         set->task_ndiag[t] > 1,
-                                         set->h_tasks[t].nitems, set->block, ctx->stream));
+        HIPCHK(ctx, launch_sample_order(a, set->tasks[t].order, set->q, ctx->desc.precision,
+                                        set->task_ndiag[t] > 1, t, -1, set->h_tasks[t].nitems,
+                                        set->block, ctx->stream));
         if (timed) timed_end(ctx, slot);
       }
       HIPCHK(ctx, launch_finish(a, 0, nt, 0, alpha, ctx->stream));
@@ -1204,17 +1204,7 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
     return MBPT_OK;
   }
   const bool persistent = set->launch_mode == MBPT_LAUNCH_PERSISTENT;
-  // fourth-order nuclear-matter single diagrams with the quartic regulator,
-  // the polynomial label sums and the free spectrum take the per-diagram
-  // kernels (compile-time masks): one launch per diagram of the order's range
-  // (the tasks are numbered by diagram, see mbpt_integrate)
   const int prec = ctx->desc.precision;
-  auto fixed4 = [&](const OrderRange &r) {
-    return !persistent && r.order == 4 && set->q == 4 && !r.group && ctx->desc.label_mode == 0 &&
-           a.phys.half_exp == 2 && a.phys.spectrum == MBPT_SPECTRUM_FREE && a.nreg == 0 &&
-           (prec == MBPT_FP64 || prec == MBPT_FP32);
-  };
-  auto id_of = [&](int k) { return set->diags[set->task_diag[set->olist[k].y]].id; };
   for (int it = 0; it < iters; ++it) {
     size_t slot = 0;
     if (timed) timed_begin(ctx, slot);
@@ -1222,16 +1212,6 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
       if (persistent) {
         HIPCHK(ctx, launch_sample_persistent(a, r.order, set->q, prec, r.group, r.k0, r.k1,
                                              r.nitems, set->block, ctx->num_cus, ctx->stream));
-      } else if (fixed4(r)) {
-        for (int ka = r.k0; ka < r.k1;) {
-          const int id = id_of(ka);
-          int kb = ka + 1;
-          while (kb < r.k1 && id_of(kb) == id) ++kb;
-          const int end = kb < r.k1 ? set->olist[kb].x : r.item_end;
-          HIPCHK(ctx, launch_sample_order_fixed4(a, id, prec == MBPT_FP32 ? 1 : 0, ka, kb,
-                                                 end - set->olist[ka].x, set->block, ctx->stream));
-          ka = kb;
-        }
       } else {
         HIPCHK(ctx, launch_sample_order(a, r.order, set->q, prec, r.group, r.k0, r.k1, r.nitems,
                                         set->block, ctx->stream));

@@ -1,0 +1,60 @@
+"""The sample kernels at the sizes where work items, wavefronts and queues
+end: the first iteration (uniform grid) of a task set equals the mean and the
+variance of the oracle's weights of the same samples.  The bounds are the
+per-sample ones, averaged: |I - mean w| <= mean(tol W_cond), and for the
+variance twice that of every |w - mean w|."""
+import numpy as np
+import pytest
+
+import oracle as O
+
+from test_gpu_parity import Run, _task
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_24532_amd as M
+    M.lib()
+    return M
+
+
+def _check_first_iteration(M, cases, N, precision, mode, block, spt):
+    tasks = [_task(o, d, q, n, x, 11 + k) for k, (o, d, q, n, x) in enumerate(cases)]
+    run = Run(M, tasks, max_samples=max(N, 2), mode=mode, block=block, spt=spt,
+              precision=M.MBPT_FP32 if precision == "fp32" else M.MBPT_FP64)
+    try:
+        per, _ = M.mbpt_integrate(run.set, N, 1)
+        logs = [M.mbpt_iteration_log(run.set, k) for k in range(len(tasks))]
+    finally:
+        run.close()
+    tol = 1e-5 if precision == "fp32" else 1e-12
+    for k, (o, d, q, n, x) in enumerate(cases):
+        pb = O.problem(o, d, density=n, proton_fraction=x, q=q, seed=1, task_key=11 + k,
+                       label_method=1 if q == 4 and o >= 4 else 0)
+        w, cond = O.sample_values(pb, O.uniform_grid(3 * (o + 1)), 0, 0, N)
+        I, V = logs[k][0][0], logs[k][1][0]
+        slack = 1e-14 * np.abs(w).mean() + 1e-300
+        assert per[k].n_evals == N
+        assert abs(I - w.mean()) <= tol * cond.mean() + slack, (o, d, q, x, I, w.mean())
+        dev = w - w.mean()
+        want = (dev * dev).mean() / (N - 1)
+        bound = 2 * (np.abs(dev) * (tol * (cond + cond.mean()) + slack)).mean() / (N - 1)
+        bound += 1e-12 * ((w * w).mean() / (N - 1)) + (tol * cond).max() ** 2 / (N - 1)
+        assert abs(V - want) <= bound, (o, d, q, x, V, want)
+
+
+ALL4 = [(4, d, 4, 0.16, (0.0, 0.25, 0.5, 0.8)[d % 4]) for d in range(39)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("mode,N,block,spt", [(0, 257, 256, 1), (1, 2, 64, 1), (1, 2049, 256, 16)])
+def test_every_fourth_order_diagram(M, precision, mode, N, block, spt):
+    """All 39 diagrams through the kernel that holds them, one launch per task
+    and one launch for all, at proton fractions 0 to 0.8."""
+    print(f"case all o4 {precision} mode={mode} N={N}", flush=True)
+    _check_first_iteration(M, ALL4, N, precision, mode, block, spt)
