@@ -69,8 +69,8 @@ __device__ __forceinline__ void load_turn_table(SinCos *dst, double *ex) {
 
 // What the integrand reads from LDS: the turn table, the 2^(j/64) table, the
 // HF spline entries of the task (ntab isospin tables of kHfEntries x 4
-// doubles, absent with the free spectrum) and the grid pairs (e_b + w_b 2^-33,
-// w_b).  Block layout: turn table, 2^(j/64) table, HF tables, grid pairs, then
+// doubles, absent with the free spectrum) and the grid pairs of grid_pair.
+// Block layout: turn table, 2^(j/64) table, HF tables, grid pairs, then
 // the kernel's own scratch.
 struct SampleLds {
   const SinCos *turn;
@@ -214,13 +214,12 @@ __device__ __forceinline__ double hf_sigma(const double *__restrict__ hf, int ta
   return fma(t, fma(t, fma(t, e[3], e[2]), e[1]), e[0]);
 }
 
-// sin(2 pi x) and cos(2 pi x) for x in [0, 1]: the nearest table angle
+// sin and cos of 2 pi u / 128 for u in [0, 128]: the nearest table angle
 // 2 pi k / 128 rotated by the residual d, |d| <= pi / 128, whose sine and
 // cosine - 1 come from their Taylor series (first omitted terms below 4e-19
 // relative to sin d and 4e-18 absolute for cos d).
-__device__ __forceinline__ void sincos_turn(const SinCos *__restrict__ tab, double x, double &s,
+__device__ __forceinline__ void sincos_turn(const SinCos *__restrict__ tab, double u, double &s,
                                             double &c) {
-  const double u = x * static_cast<double>(MBPT_TURN_STEPS);  // exact
   const double kf = rint(u);
   const double d = (u - kf) * (2.0 * M_PI / MBPT_TURN_STEPS);  // u - kf exact
   const double z = d * d;
@@ -230,8 +229,7 @@ __device__ __forceinline__ void sincos_turn(const SinCos *__restrict__ tab, doub
   double pc = fma(z, -1.0 / 720.0, 1.0 / 24.0);
   pc = fma(z, pc, -0.5);
   const double cm = z * pc;
-  const int k = min(max(static_cast<int>(kf), 0), MBPT_TURN_STEPS);
-  const SinCos t = tab[k];
+  const SinCos t = tab[static_cast<int>(kf)];
   s = fma(t.s, cm, fma(t.c, sd, t.s));
   c = fma(t.c, cm, fma(-t.s, sd, t.c));
 }
@@ -336,11 +334,6 @@ __device__ __forceinline__ uint32_t part_mask_of(const DiagDev *__restrict__ D) 
   if constexpr (FixedMasks<ORDER, V>::kFixed) return FixedMasks<ORDER, V>::part_mask;
   else return D->part_mask;
 }
-template <int ORDER, int V>
-__device__ __forceinline__ bool loop_part_of(const DiagDev *__restrict__ D, int j) {
-  if constexpr (FixedMasks<ORDER, V>::kFixed) return FixedMasks<ORDER, V>::loop_part[j] != 0;
-  else return D->loop_part[j] != 0;
-}
 
 // Runs f(std::integral_constant<int, V>) with the diagram variant of a task
 // whose first descriptor is D: the one diagram of orders 1-2 (also as a
@@ -405,6 +398,15 @@ __device__ __forceinline__ double sqrt_normal(double a) {
   return fma(d, h, g);
 }
 
+// The same in fp32 (rsq, then one Newton correction: within an ulp of the
+// root), a clamped to 1e-30.
+__device__ __forceinline__ float sqrt_normal_f(float a) {
+  a = fmaxf(a, 1e-30f);
+  const float y = __builtin_amdgcn_rsqf(a);
+  const float g = a * y;
+  return fmaf(fmaf(-g, g, a), 0.5f * y, g);
+}
+
 // (s, c) += (s2, c2) with the rounding error of the leading parts kept
 __device__ __forceinline__ void pair_merge(double &s, double &c, double s2, double c2) {
   const double t = s + s2;
@@ -418,34 +420,56 @@ __device__ __forceinline__ void pair_merge(double &s, double &c, double s2, doub
 // Per-sample integrand in fp64.  Returns the weight; writes the VEGAS bin of
 // every dimension to bins[].
 
-// Philox words -> VEGAS bins and mapped coordinates x (fp64, identical for
-// both integrand precisions).  Returns the VEGAS Jacobian.
+// Grid pair of bin b of dimension m (radius, cosine and azimuth of each loop
+// in turn): with the bin's lower edge e, width w and a random word's fraction
+// r = (f + 1/2) 2^-32, f whole, the mapped coordinate x = e + r w is one fma of
+// f with the pair, scaled to what the loop momentum is built from: the radius
+// R x0, the cosine 2 x1 - 1, and the azimuth in turns, or (AZ) in table steps
+// of the turn.  Scaling here, once per work item, takes a multiplication per
+// coordinate and the fraction's conversion to [0, 1) out of every sample; on
+// MI355X (with the one-product bin split of vegas_map and the short fp32 root)
+// orders 2+3, 36 tasks x 2^24 fp32, 7.67 -> 6.95 ms per iteration, and the 585
+// fourth-order tasks fp32 (2^21) 24.8 -> 22.9 ms, fp64 (500 009) 7.1 -> 6.6 ms.
+template <bool AZ>
+__device__ __forceinline__ double2 grid_pair(int m, double e0, double e1, double R) {
+  const double w = e1 - e0;
+  const double e = fma(w, 0x1p-33, e0);
+  const double ws = w * 0x1p-32;
+  const int role = m % 3;
+  if (role == 0) return make_double2(R * e, R * ws);
+  if (role == 1) return make_double2(fma(2.0, e, -1.0), 2.0 * ws);
+  return AZ ? make_double2(MBPT_TURN_STEPS * e, MBPT_TURN_STEPS * ws) : make_double2(e, ws);
+}
+
+// Radius of the sphere loop j of the task's first descriptor D is drawn from.
+__device__ __forceinline__ double loop_radius(const TaskDev *__restrict__ T,
+                                              const DiagDev *__restrict__ D, int j) {
+  return D->loop_part[j] ? T->Rp : T->Rh;
+}
+
+// Philox words -> VEGAS bins and scaled coordinates (see grid_pair; fp64,
+// identical for both integrand precisions).  Returns jc times the product of
+// the pairs' widths, the VEGAS Jacobian.
 template <int ND>
 __device__ __forceinline__ double vegas_map(const KArgs &a, const TaskDev *__restrict__ T,
-                                            const double2 *__restrict__ g, uint64_t s,
+                                            const double2 *__restrict__ g, double jc, uint64_t s,
                                             uint32_t iter, double *x, int *bins) {
   constexpr int NW = (ND + 3) / 4;
-  const int nb = a.phys.nb;
+  const uint32_t nb = static_cast<uint32_t>(a.phys.nb);
   // counter (s lo, s hi, iteration, word block), key (seed, task)
   uint32_t wd[4 * NW];
 #pragma unroll
   for (int j = 0; j < NW; ++j)
     philox4x32_10(static_cast<uint32_t>(s), static_cast<uint32_t>(s >> 32), iter,
                   static_cast<uint32_t>(j), a.phys.seed, T->key, wd + 4 * j);
-  // bin b = floor(w nb / 2^32), fraction ((w nb mod 2^32) + 1/2) / 2^32.
-  // y = w nb 2^-32 is exact in fp64 (at most 39 significant bits), so b (the
-  // truncation of y >= 0) and y - b (v_fract_f64) come out exactly; the half
-  // is folded into the grid pair's first entry, e_b + w_b 2^-33.  Returns
-  // prod_m width_m; the factor nb^ND is in jac_const.
-  double jac = 1.0;
-  const double nbscale = static_cast<double>(nb) * 0x1p-32;
+  // w nb = b 2^32 + f: bin b and fraction f from one 32 x 32 product
+  double jac = jc;
 #pragma unroll
   for (int m = 0; m < ND; ++m) {
-    const double y = static_cast<double>(wd[m]) * nbscale;
-    const int b = static_cast<int>(y);
-    const double r = __builtin_amdgcn_fract(y);
+    const uint64_t y = static_cast<uint64_t>(wd[m]) * nb;
+    const int b = static_cast<int>(y >> 32);
     const double2 ew = g[m * nb + b];
-    x[m] = fma(r, ew.y, ew.x);
+    x[m] = fma(static_cast<double>(static_cast<uint32_t>(y)), ew.y, ew.x);
     jac *= ew.y;
     bins[m] = b;
   }
@@ -453,22 +477,73 @@ __device__ __forceinline__ double vegas_map(const KArgs &a, const TaskDev *__res
 }
 
 // Sample-independent part of the Jacobian of a task (uniform, hoisted out of
-// the sample loops): nb^ND from the VEGAS map, 4 pi R_j^3 per loop from the
-// spherical map (the rest, x0_j^2, is per sample), and 1/n.
-template <int ORDER, int V>
-__device__ __forceinline__ double jac_const(const KArgs &a, const TaskDev *__restrict__ T,
-                                            const DiagDev *__restrict__ D) {
+// the sample loops): nb^ND prod_m w_m from the VEGAS map times 4 pi R_j rad_j^2
+// per loop from the spherical map, times 1/n, where the product of the grid
+// pairs' widths holds prod_m w_m 2^-32, R_j per radius, 2 per cosine and (AZ)
+// MBPT_TURN_STEPS per azimuth, and rad_j^2 is per sample.  (The large power of
+// two comes in first, so no partial product leaves the normal range.)
+template <int ORDER, bool AZ>
+__device__ __forceinline__ double jac_const(const KArgs &a, const TaskDev *__restrict__ T) {
   constexpr int L = ORDER + 1;
   double c = T->inv_density;
-  const double nb = static_cast<double>(a.phys.nb);
+  const double nb = static_cast<double>(a.phys.nb) * 0x1p32;
 #pragma unroll
   for (int m = 0; m < 3 * L; ++m) c *= nb;
 #pragma unroll
-  for (int j = 0; j < L; ++j) {
-    const double R = loop_part_of<ORDER, V>(D, j) ? T->Rp : T->Rh;
-    c *= (4.0 * M_PI) * R * R * R;
-  }
+  for (int j = 0; j < L; ++j) c *= (4.0 * M_PI) / (2.0 * (AZ ? MBPT_TURN_STEPS : 1.0));
   return c;
+}
+
+// Loop momenta of a sample: radius, cos theta and azimuth from the map, the
+// squares of the radii, and the whole Jacobian.  The azimuth's sine and cosine
+// come from the turn table in fp64 and from the hardware (in revolutions) in
+// fp32.
+template <int ORDER, bool AZ>
+__device__ __forceinline__ double loop_momenta(const KArgs &a, const TaskDev *__restrict__ T,
+                                               const SampleLds &Ls, double jc, uint64_t s,
+                                               uint32_t iter, int *bins, double (*k)[3],
+                                               double *r2) {
+  constexpr int L = ORDER + 1;
+  double x[3 * L];
+  const double jac = vegas_map<3 * L>(a, T, Ls.g, jc, s, iter, x, bins);
+  double rp = 1.0;
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    const double rad = x[3 * j], ct = x[3 * j + 1];
+    const double st = sqrt_normal((1.0 - ct) * (1.0 + ct));
+    double sp, cp;
+    sincos_turn(Ls.turn, AZ ? x[3 * j + 2] : x[3 * j + 2] * MBPT_TURN_STEPS, sp, cp);
+    const double rs = rad * st;
+    k[j][0] = rs * cp;
+    k[j][1] = rs * sp;
+    k[j][2] = rad * ct;
+    r2[j] = rad * rad;
+    rp = j == 0 ? rad : rp * rad;
+  }
+  return jac * (rp * rp);
+}
+template <int ORDER, bool AZ>
+__device__ __forceinline__ double loop_momenta(const KArgs &a, const TaskDev *__restrict__ T,
+                                               const SampleLds &Ls, double jc, uint64_t s,
+                                               uint32_t iter, int *bins, float (*k)[3], float *r2) {
+  static_assert(!AZ, "the fp32 azimuth is taken in revolutions");
+  constexpr int L = ORDER + 1;
+  double x[3 * L];
+  const double jac = vegas_map<3 * L>(a, T, Ls.g, jc, s, iter, x, bins);
+  double rp = 1.0;
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    const float rad = static_cast<float>(x[3 * j]), ct = static_cast<float>(x[3 * j + 1]);
+    const float st = sqrt_normal_f((1.0f - ct) * (1.0f + ct));
+    const float rev = static_cast<float>(x[3 * j + 2]);
+    const float rs = rad * st;
+    k[j][0] = rs * __builtin_amdgcn_cosf(rev);
+    k[j][1] = rs * __builtin_amdgcn_sinf(rev);
+    k[j][2] = rad * ct;
+    r2[j] = rad * rad;
+    rp = j == 0 ? x[3 * j] : rp * x[3 * j];
+  }
+  return jac * (rp * rp);
 }
 
 // True if some label assignment survives the Pauli factors: neutron matter
@@ -835,7 +910,7 @@ template <int ORDER, int Q, bool HF, bool REG, bool X, bool PI, int V, int HE = 
 __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *__restrict__ T,
                                                 const DiagDev *__restrict__ D,
                                                 const SampleLds &Ls, const double (*k)[3],
-                                                uint32_t &npass, uint32_t &nterms, double *wr) {
+                                                const double *r2, uint32_t &npass, uint32_t &nterms, double *wr) {
   constexpr int L = ORDER + 1;
   constexpr int NL = 2 * ORDER;
   constexpr int NC = ORDER - 1;
@@ -856,7 +931,9 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
       if constexpr (TD) table_sum<L>(D->coef_d[l], k, kv);
       else masked_sum<L, false, FixedMasks<ORDER, V>::kFixed>(lmask_of<ORDER, V>(D, l), k, kv);
     }
-    const double k2 = kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
+    // (a loop line's k^2 is its squared radius)
+    const double k2 = l < L ? r2[l < L ? l : 0]
+                            : kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
     eps[l] = a.phys.hb2m * k2;
     deps[l] = 0.0;
     if constexpr (HF) {
@@ -999,34 +1076,15 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
 // REG: the regularised components go to wr[0..nreg) (Jacobian and 1/n
 // included).
 template <int ORDER, int Q, bool HF, bool G, bool X, bool PI, int V, bool REG = false, int HE = 0,
-          bool SCR = false, bool TD = false>
+          bool SCR = false, bool TD = false, bool AZ = true>
 __device__ __forceinline__ double eval_fp64(const KArgs &a, const TaskDev *__restrict__ T,
                                             const DiagDev *__restrict__ D,
                                             const SampleLds &Ls, double jc, uint64_t s,
                                             uint32_t iter, int *bins, uint32_t &npass,
                                             uint32_t &nterms, double *wr = nullptr) {
   constexpr int L = ORDER + 1;
-  constexpr int ND = 3 * L;
-  double x[ND];
-  double jac = vegas_map<ND>(a, T, Ls.g, s, iter, x, bins);
-
-  // loop momenta: radius R x0, cos theta = 2 x1 - 1, azimuth 2 pi x2
-  // (Jacobian 4 pi R^3 x0^2 per loop)
-  double k[L][3];
-  double x0p = 1.0;  // prod_j x0_j
-#pragma unroll
-  for (int j = 0; j < L; ++j) {
-    const double R = loop_part_of<ORDER, V>(D, j) ? T->Rp : T->Rh;
-    const double rad = R * x[3 * j];
-    const double ct = 2.0 * x[3 * j + 1] - 1.0;
-    const double st = sqrt_normal((1.0 - ct) * (1.0 + ct));
-    double sp, cp;
-    sincos_turn(Ls.turn, x[3 * j + 2], sp, cp);
-    k[j][0] = rad * st * cp;
-    k[j][1] = rad * st * sp;
-    k[j][2] = rad * ct;
-    x0p *= x[3 * j];
-  }
+  double k[L][3], r2[L];
+  const double scale = loop_momenta<ORDER, AZ>(a, T, Ls, jc, s, iter, bins, k, r2);
   if constexpr (REG)
     for (int r = 0; r < kMaxReg; ++r) wr[r] = 0.0;
   double sum;
@@ -1040,19 +1098,18 @@ __device__ __forceinline__ double eval_fp64(const KArgs &a, const TaskDev *__res
         SampleLds Lm = Ls;  // the member's cycle table
         Lm.cyc = static_cast<const char *>(Ls.cyc) + di * cycle_table_bytes<ORDER>();
         sum += diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, true, false, TDG>(
-            a, T, D + di, Lm, k, npass, nterms, wr);
+            a, T, D + di, Lm, k, r2, npass, nterms, wr);
       } else {
         sum += diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, false, false, TDG>(
-            a, T, D + di, Ls, k, npass, nterms, wr);
+            a, T, D + di, Ls, k, r2, npass, nterms, wr);
       }
     }
   } else {
     constexpr bool CY = cycle_form<ORDER, Q, false, X, HF>();
-    sum = diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, CY, SCR, TD>(a, T, D, Ls, k, npass,
+    sum = diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, CY, SCR, TD>(a, T, D, Ls, k, r2, npass,
                                                                     nterms, wr);
     if constexpr (SCR) return sum;
   }
-  const double scale = jac * (x0p * x0p) * jc;
   if constexpr (REG)
     for (int r = 0; r < kMaxReg; ++r) wr[r] *= scale;
   return scale * sum;
@@ -1100,7 +1157,7 @@ template <int ORDER, int Q, bool X, int V, int HE = 0, bool CY = false, bool SCR
 __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *__restrict__ T,
                                                 const DiagDev *__restrict__ D,
                                                 const SampleLds &Ls, const float (*k)[3],
-                                                uint32_t &npass, uint32_t &nterms,
+                                                const float *r2, uint32_t &npass, uint32_t &nterms,
                                                 bool &fallback) {
   constexpr int L = ORDER + 1;
   constexpr int NL = 2 * ORDER;
@@ -1122,7 +1179,8 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
       if constexpr (TD) table_sum_f<L>(D->coef_f[l], k, kv);
       else masked_sum_f<L, false, FixedMasks<ORDER, V>::kFixed>(lmask_of<ORDER, V>(D, l), k, kv);
     }
-    const float k2 = kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
+    const float k2 = l < L ? r2[l < L ? l : 0]
+                           : kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
     eps[l] = hb2m * k2;
     near |= fabsf(k2 - kFn2) < bandk * kFn2;
     inN |= (k2 < kFn2) ? (1u << l) : 0u;
@@ -1272,28 +1330,8 @@ __device__ __forceinline__ double eval_fp32(const KArgs &a, const TaskDev *__res
                                             uint32_t iter, int *bins, uint32_t &npass,
                                             uint32_t &nterms, bool &fallback) {
   constexpr int L = ORDER + 1;
-  constexpr int ND = 3 * L;
-  double x[ND];
-  double jac = vegas_map<ND>(a, T, Ls.g, s, iter, x, bins);
-
-  // loop momenta; the azimuth goes to the hardware sine/cosine in revolutions
-  float k[L][3];
-  double x0p = 1.0;  // prod_j x0_j
-#pragma unroll
-  for (int j = 0; j < L; ++j) {
-    const double R = loop_part_of<ORDER, V>(D, j) ? T->Rp : T->Rh;
-    const double rad64 = R * x[3 * j];
-    x0p *= x[3 * j];
-    const float rad = static_cast<float>(rad64);
-    const float ct = static_cast<float>(2.0 * x[3 * j + 1] - 1.0);
-    const float st = __builtin_sqrtf(fmaxf(0.0f, (1.0f - ct) * (1.0f + ct)));
-    const float rev = static_cast<float>(x[3 * j + 2]);
-    const float sp = __builtin_amdgcn_sinf(rev), cp = __builtin_amdgcn_cosf(rev);
-    const float rs = rad * st;
-    k[j][0] = rs * cp;
-    k[j][1] = rs * sp;
-    k[j][2] = rad * ct;
-  }
+  float k[L][3], r2[L];
+  const double scale = loop_momenta<ORDER, false>(a, T, Ls, jc, s, iter, bins, k, r2);
   double sum;
   if constexpr (G) {
     sum = 0.0;
@@ -1306,10 +1344,10 @@ __device__ __forceinline__ double eval_fp32(const KArgs &a, const TaskDev *__res
       if constexpr (group_cycle_form<ORDER, Q, X, false>()) {
         SampleLds Lm = Ls;  // the member's cycle table
         Lm.cyc = static_cast<const char *>(Ls.cyc) + di * cycle_table_bytes<ORDER>();
-        sum += diag_weight32<ORDER, Q, X, V, HE, true, false, TDG>(a, T, D + di, Lm, k, gpass,
+        sum += diag_weight32<ORDER, Q, X, V, HE, true, false, TDG>(a, T, D + di, Lm, k, r2, gpass,
                                                                     gterms, fallback);
       } else {
-        sum += diag_weight32<ORDER, Q, X, V, HE, false, false, TDG>(a, T, D + di, Ls, k, gpass,
+        sum += diag_weight32<ORDER, Q, X, V, HE, false, false, TDG>(a, T, D + di, Ls, k, r2, gpass,
                                                                      gterms, fallback);
       }
       if (fallback) return 0.0;  // the whole sample is re-evaluated in fp64
@@ -1318,11 +1356,11 @@ __device__ __forceinline__ double eval_fp32(const KArgs &a, const TaskDev *__res
     nterms += gterms;
   } else {
     constexpr bool CY = cycle_form<ORDER, Q, false, X, false>();
-    sum = diag_weight32<ORDER, Q, X, V, HE, CY, SCR, TD>(a, T, D, Ls, k, npass, nterms, fallback);
+    sum = diag_weight32<ORDER, Q, X, V, HE, CY, SCR, TD>(a, T, D, Ls, k, r2, npass, nterms, fallback);
     if constexpr (SCR) return sum;
     if (fallback) return 0.0;
   }
-  return jac * (x0p * x0p) * jc * sum;
+  return scale * sum;
 }
 
 // Kernel mode P: 0 fp64; 1 fp32 with the fp64 fallback; 2 fp64 with the
@@ -1340,6 +1378,11 @@ constexpr bool group_of() {
 template <int P>
 constexpr bool reg_of() {
   return P >= 5;
+}
+// Azimuths as steps of the turn table (see grid_pair): the fp64 kernels.
+template <int P>
+constexpr bool az_steps() {
+  return prec_of<P>() != 1;
 }
 // Per-vertex-pair inversion (see diag_weight64) where the registers it frees
 // give the kernel one more wave per SIMD: the third-order fp32 kernels (their
@@ -1363,16 +1406,17 @@ __device__ __forceinline__ double eval_sample(const KArgs &a, const TaskDev *__r
   double w = 0.0;
   with_variant<ORDER, G, cycle_form<ORDER, Q, G, X, PP == 2>()>(D, [&](auto vt) {
     constexpr int V = decltype(vt)::value;
-    const double jc = jac_const<ORDER, V>(a, T, D);
+    constexpr bool AZ = az_steps<P>();
+    const double jc = jac_const<ORDER, AZ>(a, T);
     if (PP != 1) {
-      w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
       return;
     }
     bool fb = false;
     w = eval_fp32<ORDER, Q, G, X, V, HE>(a, T, D, Ls, jc, s, iter, bins, npass, nterms, fb);
     if (fb) {
       ++nfb;
-      w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
     }
   });
   return w;
@@ -1492,7 +1536,7 @@ __device__ __forceinline__ void block_lds(const KArgs &a, double *smem, BlockLds
 }
 
 // Loads task t's tables into the block's LDS: HF spline entries, grid pairs
-// (e_b + w_b 2^-33, w_b), a zeroed histogram and the label-cycle table(s) of
+// (grid_pair), a zeroed histogram and the label-cycle table(s) of
 // its diagram(s).  The caller synchronises before and after.
 template <int ORDER, int Q, int P, bool X>
 __device__ __forceinline__ void task_lds(const KArgs &a, int t, BlockLds &B) {
@@ -1508,10 +1552,11 @@ __device__ __forceinline__ void task_lds(const KArgs &a, int t, BlockLds &B) {
     for (int i = tid; i < n; i += bs) hf[i] = src[i];
   }
   const double *ge = a.grids + T->grid_off;
+  const DiagDev *__restrict__ D = a.diags + T->diag;
   for (int i = tid; i < ND * nb; i += bs) {
     const int m = i / nb, b = i - m * nb;
     const double e0 = ge[m * (nb + 1) + b], e1 = ge[m * (nb + 1) + b + 1];
-    B.g[i] = make_double2(fma(e1 - e0, 0x1p-33, e0), e1 - e0);
+    B.g[i] = grid_pair<az_steps<P>()>(m, e0, e1, loop_radius(T, D, m / 3));
     B.h[i] = 0.0;
   }
   if constexpr (holds_cycles<ORDER, Q, P, X>())
@@ -1586,14 +1631,15 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
     constexpr int V = decltype(vt)::value;
     // the loop coefficients decoded in the descriptor (desc_coef)
     constexpr bool TD = desc_coef<ORDER, P>() && !FixedMasks<ORDER, V>::kFixed;
-    const double jc = jac_const<ORDER, V>(a, T, D);
+    constexpr bool AZ = az_steps<P>();
+    const double jc = jac_const<ORDER, AZ>(a, T);
     if constexpr (SCR && PP == 0) {
       int pn = 0;  // wave-uniform
       auto drain_pass = [&](int take) {
         if (lane < take) {
           const uint64_t s = base + pqueue[lane];
           int bins[ND];
-          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD>(
+          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD, AZ>(
               a, T, D, Ls, jc, s, iter, bins, npass, nterms);
           accumulate(w, bins);
         }
@@ -1604,7 +1650,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         bool go = false;
         if (s < N) {
           int bins[ND];
-          go = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, true, TD>(
+          go = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, true, TD, AZ>(
                    a, T, D, Ls, jc, s, iter, bins, npass, nterms) != 0.0;
           if (!go) accumulate_zero();
         }
@@ -1619,7 +1665,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
           int bins[ND];
           if constexpr (R) {
             double wr[kMaxReg];
-            const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, true, HE, false, TD>(
+            const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, true, HE, false, TD, AZ>(
                 a, T, D, Ls, jc, s, iter, bins, npass, nterms, wr);
             accumulate(w, bins);
             // the extrapolation's weights sum to one, so its shifted value
@@ -1635,7 +1681,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
             rs[2 * kMaxReg] += dx;
             rs[2 * kMaxReg + 1] += dx * dx;
           } else {
-            const double w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE, false, TD>(
+            const double w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE, false, TD, AZ>(
                 a, T, D, Ls, jc, s, iter, bins, npass, nterms);
             accumulate(w, bins);
           }
@@ -1650,7 +1696,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         if (lane < take) {
           const uint64_t s = base + queue[lane];
           int bins[ND];
-          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD>(
+          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD, AZ>(
               a, T, D, Ls, jc, s, iter, bins, npass, nterms);
           accumulate(w, bins);
         }
@@ -1956,7 +2002,7 @@ __global__ __launch_bounds__(256) void dump_samples(KArgs a, int t, uint32_t ite
   for (int i = threadIdx.x; i < ND * nb; i += blockDim.x) {
     const int m = i / nb, b = i - m * nb;
     const double e0 = ge[m * (nb + 1) + b], e1 = ge[m * (nb + 1) + b + 1];
-    g[i] = make_double2(fma(e1 - e0, 0x1p-33, e0), e1 - e0);
+    g[i] = grid_pair<az_steps<P>()>(m, e0, e1, loop_radius(T, D, m / 3));
   }
   if constexpr (holds_cycles<ORDER, Q, P, X>()) {
     void *tab = g + ND * nb;
@@ -1974,7 +2020,7 @@ __global__ __launch_bounds__(256) void dump_samples(KArgs a, int t, uint32_t ite
           D, [&](auto vt) {
         constexpr int V = decltype(vt)::value;
         out[i] = eval_fp64<ORDER, Q, false, group_of<P>(), X, PI, V, true, HE>(
-            a, T, D, Ls, jac_const<ORDER, V>(a, T, D), first + i, iter, bins, np, nt, wr);
+            a, T, D, Ls, jac_const<ORDER, true>(a, T), first + i, iter, bins, np, nt, wr);
       });
       if (out_reg)
         for (int r = 0; r < a.nreg; ++r) out_reg[i * a.nreg + r] = wr[r];
