@@ -49,8 +49,7 @@ struct alignas(16) DiagDev {
   uint32_t cyc_mask[kMaxCycles];
   uint64_t cyc_e[32];
   uint32_t cyc_e32[32];
-  // The loop coefficients of lmask / pmask_v / qmask_v decoded (the vertex
-  // sums halved): sum s < 2 order is line slot s, then (2p, 2p') of each
+  // The loop coefficients of lmask / pmask_v / qmask_v decoded: sum s < 2 order is line slot s, then (2p, 2p') of each
   // vertex; fp64, then fp32.  The group kernels, whose member loop runs at
   // run time, read them through the scalar cache instead of decoding the
   // masks per sum and sample.
@@ -193,6 +192,8 @@ struct Phys {
   double Vy;        // Cy * hbarc      [MeV fm^3 * fm^-2]
   double m2;        // mpi^2
   double invLn;     // Lambda^{-reg_exp}
+  double quarter_n; // 4^{-reg_exp / 2}: (2p)^n to p^n
+  double vscale;    // scale of the interaction, |V0| + |Vy| / m2 (1 if that is 0)
   double hb2m;      // hbar^2 / 2m
   int half_exp;     // reg_exp / 2
   int nb;           // bins per dimension

@@ -234,67 +234,77 @@ __device__ __forceinline__ void sincos_turn(const SinCos *__restrict__ tab, doub
   c = fma(t.c, cm, fma(-t.s, sd, t.c));
 }
 
+template <typename F>
+__device__ __forceinline__ F fma_t(F x, F y, F z) {
+  return __builtin_fma(x, y, z);
+}
+template <>
+__device__ __forceinline__ float fma_t<float>(float x, float y, float z) {
+  return __builtin_fmaf(x, y, z);
+}
+
 // Coefficient c in {0, +-1, +-2} of loop j in the uniform bitmask m (bits
-// 0-7: +1, 8-15: -1, 16-23: +2, 24-31: -2) as a double, built from its bit
-// pattern with scalar instructions only.  HALF: the coefficients halved
-// (vertex relative momenta are half the difference of two line momenta).
-template <bool HALF = false>
-__device__ __forceinline__ double mask_coef(uint32_t m, int j) {
+// 0-7: +1, 8-15: -1, 16-23: +2, 24-31: -2) in precision F, built from its bit
+// pattern with scalar instructions only.
+template <typename F>
+__device__ __forceinline__ F mask_coef(uint32_t m, int j);
+template <>
+__device__ __forceinline__ double mask_coef<double>(uint32_t m, int j) {
   uint32_t hi = 0u;
-  hi = (m & (1u << j)) ? (HALF ? 0x3FE00000u : 0x3FF00000u) : hi;
-  hi = (m & (1u << (8 + j))) ? (HALF ? 0xBFE00000u : 0xBFF00000u) : hi;
-  hi = (m & (1u << (16 + j))) ? (HALF ? 0x3FF00000u : 0x40000000u) : hi;
-  hi = (m & (1u << (24 + j))) ? (HALF ? 0xBFF00000u : 0xC0000000u) : hi;
+  hi = (m & (1u << j)) ? 0x3FF00000u : hi;
+  hi = (m & (1u << (8 + j))) ? 0xBFF00000u : hi;
+  hi = (m & (1u << (16 + j))) ? 0x40000000u : hi;
+  hi = (m & (1u << (24 + j))) ? 0xC0000000u : hi;
   return __hiloint2double(static_cast<int>(hi), 0);
 }
-
-// sum_j c_j v_j over loops j < L (coefficients from the uniform bitmask m).
-// SKIP0: m is a compile-time constant, so zero coefficients are left out
-// (an fma with a zero coefficient is not foldable under IEEE rules).
-template <int L, bool HALF = false, bool SKIP0 = false>
-__device__ __forceinline__ void masked_sum(uint32_t m, const double (*k)[3], double *out) {
-  double x = 0.0, y = 0.0, z = 0.0;
-#pragma unroll
-  for (int j = 0; j < L; ++j) {
-    const double c = mask_coef<HALF>(m, j);
-    if (SKIP0 && c == 0.0) continue;
-    x = fma(c, k[j][0], x);
-    y = fma(c, k[j][1], y);
-    z = fma(c, k[j][2], z);
-  }
-  out[0] = x;
-  out[1] = y;
-  out[2] = z;
+template <>
+__device__ __forceinline__ float mask_coef<float>(uint32_t m, int j) {
+  uint32_t bits = 0u;
+  bits = (m & (1u << j)) ? 0x3F800000u : bits;
+  bits = (m & (1u << (8 + j))) ? 0xBF800000u : bits;
+  bits = (m & (1u << (16 + j))) ? 0x40000000u : bits;
+  bits = (m & (1u << (24 + j))) ? 0xC0000000u : bits;
+  return __uint_as_float(bits);
 }
 
-// sum_j c_j v_j over loops j < L with the coefficients c read from a table:
-// the same operations, in the same order, as masked_sum of the mask they were
-// decoded from (zero coefficients included).
-template <int L>
-__device__ __forceinline__ void table_sum(const double *c, const double (*k)[3], double *out) {
-  double x = 0.0, y = 0.0, z = 0.0;
+// out = sum_j c_j v_j over loops j < L, the terms in loop order, from coef(j).
+// SKIP0: the coefficients are compile-time constants, so zero terms are left
+// out and the first one is taken as it is (under IEEE rules neither a product
+// with zero nor a sum with zero folds).
+template <int L, bool SKIP0, typename F, typename C>
+__device__ __forceinline__ void loop_sum(C &&coef, const F (*k)[3], F *out) {
+  bool first = true;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) out[i] = F(0);
 #pragma unroll
   for (int j = 0; j < L; ++j) {
-    x = fma(c[j], k[j][0], x);
-    y = fma(c[j], k[j][1], y);
-    z = fma(c[j], k[j][2], z);
+    const F c = coef(j);
+    if (SKIP0 && c == F(0)) continue;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) out[i] = first ? c * k[j][i] : fma_t<F>(c, k[j][i], out[i]);
+    first = false;
   }
-  out[0] = x;
-  out[1] = y;
-  out[2] = z;
 }
-template <int L>
-__device__ __forceinline__ void table_sum_f(const float *c, const float (*k)[3], float *out) {
-  float x = 0.0f, y = 0.0f, z = 0.0f;
-#pragma unroll
-  for (int j = 0; j < L; ++j) {
-    x = fmaf(c[j], k[j][0], x);
-    y = fmaf(c[j], k[j][1], y);
-    z = fmaf(c[j], k[j][2], z);
-  }
-  out[0] = x;
-  out[1] = y;
-  out[2] = z;
+// Coefficients from the uniform bitmask m.
+template <int L, bool SKIP0, typename F>
+__device__ __forceinline__ void masked_sum(uint32_t m, const F (*k)[3], F *out) {
+  loop_sum<L, SKIP0, F>([&](int j) { return mask_coef<F>(m, j); }, k, out);
+}
+// Coefficients from a row of the descriptor's decoded table: the operations of
+// the mask they were decoded from.
+template <int L, typename F>
+__device__ __forceinline__ void table_sum(const F *c, const F (*k)[3], F *out) {
+  loop_sum<L, false, F>([&](int j) { return c[j]; }, k, out);
+}
+template <typename F>
+__device__ __forceinline__ const F *coef_row(const DiagDev *__restrict__ D, int row);
+template <>
+__device__ __forceinline__ const double *coef_row<double>(const DiagDev *__restrict__ D, int row) {
+  return D->coef_d[row];
+}
+template <>
+__device__ __forceinline__ const float *coef_row<float>(const DiagDev *__restrict__ D, int row) {
+  return D->coef_f[row];
 }
 
 // Descriptor masks of diagram variant V: compile-time constants where
@@ -405,6 +415,16 @@ __device__ __forceinline__ float sqrt_normal_f(float a) {
   const float y = __builtin_amdgcn_rsqf(a);
   const float g = a * y;
   return fmaf(fmaf(-g, g, a), 0.5f * y, g);
+}
+
+// 1/d from the hardware reciprocal and two Newton steps (d normal and finite;
+// within about one ulp).
+__device__ __forceinline__ double rcp_newton(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  double e = fma(-d, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-d, r, 1.0);
+  return fma(r, e, r);
 }
 
 // (s, c) += (s2, c2) with the rounding error of the leading parts kept
@@ -575,14 +595,6 @@ __device__ __forceinline__ bool pauli_allowed(const KArgs &a, const DiagDev *__r
 // ORDER/2 vertices and of the rest are tabulated once per sample, so a
 // configuration costs 2^ORDER + 2^(ORDER - ORDER/2) multiply-adds however
 // many assignments it holds.  Mode 1 walks the compressed assignment list.
-template <typename F>
-__device__ __forceinline__ F fma_t(F x, F y, F z) {
-  return __builtin_fma(x, y, z);
-}
-template <>
-__device__ __forceinline__ float fma_t<float>(float x, float y, float z) {
-  return __builtin_fmaf(x, y, z);
-}
 // The 2^ORDER coefficients of a configuration in precision F (contiguous).
 template <int ORDER, typename F>
 __device__ __forceinline__ const F *coef_run(const double *block) {
@@ -721,19 +733,16 @@ __device__ __forceinline__ uint32_t popc_w(W x) {
 // allowed on all of the cycle's lines, per cycle.  With cA / cB the cycles
 // whose lines are all allowed as neutrons / protons, E's count is 0 if a
 // cycle is allowed for neither, else 2^{cycles(E) + cycles allowed for both}.
-// The monomials carry the sign (-V_e) and are tabulated as in the
+// The monomials carry the sign (nVe = -V_e) and are tabulated as in the
 // configuration form; the counts are integers, so the sum equals the sum over
 // isospin configurations up to rounding.
 template <int ORDER, typename F, bool ABS = false, int V = -1>
 __device__ __forceinline__ F label_sum_cycles(const DiagDev *__restrict__ D, const F *Vd,
-                                              const F *Ve, CycWordV<ORDER, V> cA,
+                                              const F *nVe, CycWordV<ORDER, V> cA,
                                               CycWordV<ORDER, V> cB, F *absum = nullptr) {
   using W = CycWordV<ORDER, V>;
   constexpr int H = ORDER / 2;
   constexpr int NA = 1 << H, NB = 1 << (ORDER - H);
-  F nVe[ORDER];
-#pragma unroll
-  for (int v = 0; v < ORDER; ++v) nVe[v] = -Ve[v];
   F MA[NA], MB[NB];
   monomials<H>(Vd, nVe, MA);
   monomials<ORDER - H>(Vd + H, nVe + H, MB);
@@ -812,7 +821,7 @@ __device__ __forceinline__ F label_sum(const KArgs &a, const DiagDev *__restrict
           aacc = fma_t<F>(in, AB[eb], aacc);
         }
       }
-      if constexpr (ISO) gs = static_cast<F>(static_cast<double>(gs) / group_den<ORDER, V>(D, tau, Dn, deps));
+      if constexpr (ISO) gs *= rcp_newton(group_den<ORDER, V>(D, tau, Dn, deps));
       acc += gs;
     };
     if constexpr (Q == 2 && fixed_labels<FixedMasks<ORDER, V>>::value) {
@@ -862,7 +871,7 @@ __device__ __forceinline__ F label_sum(const KArgs &a, const DiagDev *__restrict
           gs = fma_t<F>(term_mult<F>(tm), prod, gs);
           if constexpr (ABS) aacc = fma_t<F>(fabs(term_mult<F>(tm)), aprod, aacc);
         }
-        if constexpr (ISO) gs = static_cast<F>(static_cast<double>(gs) / group_den<ORDER, V>(D, tau, Dn, deps));
+        if constexpr (ISO) gs *= rcp_newton(group_den<ORDER, V>(D, tau, Dn, deps));
         acc += gs;
       }
     }
@@ -890,14 +899,56 @@ __device__ __forceinline__ double exp_nonpos(double x, const double *ex) {
   return __builtin_ldexp(fma(t, r * q, t), k >> 6);
 }
 
-// 1/d from the hardware reciprocal and two Newton steps (d normal and finite;
-// within about one ulp).
-__device__ __forceinline__ double rcp_newton(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  double e = fma(-d, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-d, r, 1.0);
-  return fma(r, e, r);
+// Vertices of one diagram at the loop momenta k.  With the relative momenta p
+// and p', the antisymmetrised matrix element's terms are V_d = V(p, p') = V0 +
+// Vy / dd and V_e = V(p, -p') = V0 + Vy / de up to their regulators, dd and de
+// = p^2 + p'^2 -+ 2 p.p' + m^2.  Every label term takes one of them per vertex,
+// so the products dd de of all vertices come out of the label sum:
+//   Vd[v] = (V0 dd + Vy) de,  Ve[v] = (V0 de + Vy) dd  (NEG: -Ve[v]),
+//   den = prod_v dd de,
+// and one reciprocal per sample divides by den and the energy denominators
+// together.  Inverting the 2n Yukawa denominators instead (prefix products
+// around one reciprocal) took 3n more multiplications and held 4n values (with
+// the loop sums' zero terms: 585 fourth-order tasks fp32 22.9 -> 21.8 ms per
+// iteration of 2^21 samples on MI355X, orders 2+3 fp32 6.95 -> 6.73 ms).  The
+// regulators come out too, as exp(-yreg), yreg = 4^n sum_v (p^n + p'^n) (n the
+// regulator exponent).  V0, Vy: the interaction, in fp32 divided by
+// Phys::vscale, so |Vd|, |Ve| <= dd de.  KY: *ky adds the Yukawa denominators'
+// condition numbers (s + 2 |p.p'|)(1 / dd + 1 / de), if rel (uniform).
+template <int ORDER, int V, int HE, bool TD, bool NEG, bool KY, typename F>
+__device__ __forceinline__ void vertex_terms(const KArgs &a, const DiagDev *__restrict__ D,
+                                             const F (*k)[3], F V0, F Vy, F *Vd, F *Ve, F &den,
+                                             F &yreg, bool rel = false, F *ky = nullptr) {
+  constexpr int L = ORDER + 1;
+  const F m2 = static_cast<F>(a.phys.m2);
+#pragma unroll
+  for (int v = 0; v < ORDER; ++v) {
+    F p[3], q[3];  // 2 p and 2 p'
+    if constexpr (TD) {
+      table_sum<L, F>(coef_row<F>(D, 2 * ORDER + 2 * v), k, p);
+      table_sum<L, F>(coef_row<F>(D, 2 * ORDER + 2 * v + 1), k, q);
+    } else {
+      masked_sum<L, FixedMasks<ORDER, V>::kFixed, F>(pmask_of<ORDER, V>(D, v), k, p);
+      masked_sum<L, FixedMasks<ORDER, V>::kFixed, F>(qmask_of<ORDER, V>(D, v), k, q);
+    }
+    const F p2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
+    const F q2 = q[0] * q[0] + q[1] * q[1] + q[2] * q[2];
+    const F pq = p[0] * q[0] + p[1] * q[1] + p[2] * q[2];
+    const F pn = reg_pow<HE>(p2, a.phys.half_exp), qn = reg_pow<HE>(q2, a.phys.half_exp);
+    yreg = v == 0 ? pn + qn : yreg + (pn + qn);
+    const F s2 = fma_t<F>(F(0.25), p2 + q2, m2);
+    const F dd = fma_t<F>(F(-0.5), pq, s2), de = fma_t<F>(F(0.5), pq, s2);
+    const F dde = dd * de;
+    Vd[v] = fma_t<F>(V0, dd, Vy) * de;
+    Ve[v] = (NEG ? fma_t<F>(-V0, de, -Vy) : fma_t<F>(V0, de, Vy)) * dd;
+    den = v == 0 ? dde : den * dde;
+    if constexpr (KY) {
+      if (rel) {
+        const F scale = fma_t<F>(F(0.5), fabs(pq), s2);
+        *ky = fma_t<F>(scale, (dd + de) * __builtin_amdgcn_rcpf(dde), *ky);
+      }
+    }
+  }
 }
 
 // Contribution of one diagram at the loop momenta k (prefactor, regulators,
@@ -905,7 +956,7 @@ __device__ __forceinline__ double rcp_newton(double d) {
 // particle energies of the Hartree-Fock spectrum (tables in LDS).
 // REG: also add the regularised components w_k = w prod_c D_c / (D_c - k eta)
 // to wr[k - 1].
-template <int ORDER, int Q, bool HF, bool REG, bool X, bool PI, int V, int HE = 0, bool CY = false,
+template <int ORDER, int Q, bool HF, bool REG, bool X, int V, int HE = 0, bool CY = false,
           bool SCR = false, bool TD = false>
 __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *__restrict__ T,
                                                 const DiagDev *__restrict__ D,
@@ -928,8 +979,8 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
       kv[1] = k[l][1];
       kv[2] = k[l][2];
     } else {
-      if constexpr (TD) table_sum<L>(D->coef_d[l], k, kv);
-      else masked_sum<L, false, FixedMasks<ORDER, V>::kFixed>(lmask_of<ORDER, V>(D, l), k, kv);
+      if constexpr (TD) table_sum<L, double>(D->coef_d[l], k, kv);
+      else masked_sum<L, FixedMasks<ORDER, V>::kFixed, double>(lmask_of<ORDER, V>(D, l), k, kv);
     }
     // (a loop line's k^2 is its squared radius)
     const double k2 = l < L ? r2[l < L ? l : 0]
@@ -985,69 +1036,10 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     dprod *= Dc;
   }
 
-  // antisymmetrised matrix elements V_d = V(p, p'), V_e = V(p, -p') without
-  // their regulators: the regulator product over all vertices factors out of
-  // every label term and is applied once, exp(-sum_v (p^n + p'^n) / Lambda^n).
-  // The 2n Yukawa denominators and the product of energy denominators are
-  // inverted together with one division (prefix products), or (PI) with one
-  // division per vertex pair (V_d, V_e) and one for the energy denominators,
-  // which keeps 4n + 2 fewer doubles live.
-  constexpr int NR = 2 * ORDER + 1;
-  constexpr bool kPairInv = PI;
-  double den[kPairInv ? 1 : NR];
-  double Vd[ORDER], Ve[ORDER];
-  double yreg = 0.0;
-#pragma unroll
-  for (int v = 0; v < ORDER; ++v) {
-    double p[3], q[3];  // relative momenta p and p'
-    if constexpr (TD) {
-      table_sum<L>(D->coef_d[2 * ORDER + 2 * v], k, p);
-      table_sum<L>(D->coef_d[2 * ORDER + 2 * v + 1], k, q);
-    } else {
-      masked_sum<L, true, FixedMasks<ORDER, V>::kFixed>(pmask_of<ORDER, V>(D, v), k, p);
-      masked_sum<L, true, FixedMasks<ORDER, V>::kFixed>(qmask_of<ORDER, V>(D, v), k, q);
-    }
-    const double p2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
-    const double q2 = q[0] * q[0] + q[1] * q[1] + q[2] * q[2];
-    const double pq = p[0] * q[0] + p[1] * q[1] + p[2] * q[2];
-    const double pn = reg_pow<HE>(p2, a.phys.half_exp), qn = reg_pow<HE>(q2, a.phys.half_exp);
-    yreg = v == 0 ? pn + qn : yreg + (pn + qn);
-    const double s2 = p2 + q2 + a.phys.m2;
-    const double dd = s2 - 2.0 * pq, de = s2 + 2.0 * pq;
-    if constexpr (kPairInv) {
-      const double r = rcp_newton(dd * de);
-      Vd[v] = a.phys.V0 + a.phys.Vy * (de * r);
-      Ve[v] = a.phys.V0 + a.phys.Vy * (dd * r);
-    } else {
-      den[2 * v] = dd;
-      den[2 * v + 1] = de;
-    }
-  }
-  double rden;  // 1 / prod_c D_c (1 when the label sum divides per configuration)
-  if constexpr (kPairInv) {
-    rden = iso_den ? 1.0 : rcp_newton(dprod);
-  } else {
-    den[NR - 1] = iso_den ? 1.0 : dprod;
-    double pre[NR];
-    pre[0] = den[0];
-#pragma unroll
-    for (int i = 1; i < NR; ++i) pre[i] = pre[i - 1] * den[i];
-    double inv = rcp_newton(pre[NR - 1]);
-    double rinv[NR];
-#pragma unroll
-    for (int i = NR - 1; i > 0; --i) {
-      rinv[i] = inv * pre[i - 1];
-      inv *= den[i];
-    }
-    rinv[0] = inv;
-#pragma unroll
-    for (int v = 0; v < ORDER; ++v) {
-      Vd[v] = a.phys.V0 + a.phys.Vy * rinv[2 * v];
-      Ve[v] = a.phys.V0 + a.phys.Vy * rinv[2 * v + 1];
-    }
-    rden = rinv[NR - 1];
-  }
-  const double regall = exp_nonpos(-yreg * a.phys.invLn, Ls.ex);
+  double Vd[ORDER], Ve[ORDER], den, yreg;
+  vertex_terms<ORDER, V, HE, TD, CY, false, double>(a, D, k, a.phys.V0, a.phys.Vy, Vd, Ve, den,
+                                                    yreg);
+  const double regall = exp_nonpos(-yreg * (a.phys.invLn * a.phys.quarter_n), Ls.ex);
 
   double acc;
   if constexpr (CY) {
@@ -1057,17 +1049,19 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     acc = label_sum<ORDER, Q, double, iso_den, X, V>(a, D, Vd, Ve, okN, okP, lmask, nterms, Dn,
                                                      deps);
   }
-  const double base = D->pref * regall * acc;
   if constexpr (REG) {
+    const double base = D->pref * regall * acc * rcp_newton(den);
     for (int r = 0; r < a.nreg; ++r) {
       const double eta = (r + 1) * a.reg_eta;
       double pk = 1.0;
 #pragma unroll
       for (int c = 0; c < NC; ++c) pk *= Dn[c] - eta;
-      wr[r] += base / pk;
+      wr[r] = fma(base, rcp_newton(pk), wr[r]);
     }
+    return base * rcp_newton(dprod);
   }
-  return base * rden;
+  // (with isospin-dependent energies the label sum holds the denominators)
+  return D->pref * regall * acc * rcp_newton(iso_den ? den : den * dprod);
 }
 
 // One sample of a task: VEGAS map, loop momenta (radii from the first
@@ -1075,7 +1069,7 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
 // or (G) the task's T->ndiag group members summed.
 // REG: the regularised components go to wr[0..nreg) (Jacobian and 1/n
 // included).
-template <int ORDER, int Q, bool HF, bool G, bool X, bool PI, int V, bool REG = false, int HE = 0,
+template <int ORDER, int Q, bool HF, bool G, bool X, int V, bool REG = false, int HE = 0,
           bool SCR = false, bool TD = false, bool AZ = true>
 __device__ __forceinline__ double eval_fp64(const KArgs &a, const TaskDev *__restrict__ T,
                                             const DiagDev *__restrict__ D,
@@ -1097,49 +1091,22 @@ __device__ __forceinline__ double eval_fp64(const KArgs &a, const TaskDev *__res
       if constexpr (group_cycle_form<ORDER, Q, X, HF>()) {
         SampleLds Lm = Ls;  // the member's cycle table
         Lm.cyc = static_cast<const char *>(Ls.cyc) + di * cycle_table_bytes<ORDER>();
-        sum += diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, true, false, TDG>(
+        sum += diag_weight64<ORDER, Q, HF, REG, X, V, HE, true, false, TDG>(
             a, T, D + di, Lm, k, r2, npass, nterms, wr);
       } else {
-        sum += diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, false, false, TDG>(
+        sum += diag_weight64<ORDER, Q, HF, REG, X, V, HE, false, false, TDG>(
             a, T, D + di, Ls, k, r2, npass, nterms, wr);
       }
     }
   } else {
     constexpr bool CY = cycle_form<ORDER, Q, false, X, HF>();
-    sum = diag_weight64<ORDER, Q, HF, REG, X, PI, V, HE, CY, SCR, TD>(a, T, D, Ls, k, r2, npass,
+    sum = diag_weight64<ORDER, Q, HF, REG, X, V, HE, CY, SCR, TD>(a, T, D, Ls, k, r2, npass,
                                                                     nterms, wr);
     if constexpr (SCR) return sum;
   }
   if constexpr (REG)
     for (int r = 0; r < kMaxReg; ++r) wr[r] *= scale;
   return scale * sum;
-}
-
-// fp32 counterpart of masked_sum
-template <bool HALF = false>
-__device__ __forceinline__ float mask_coef_f(uint32_t m, int j) {
-  uint32_t bits = 0u;
-  bits = (m & (1u << j)) ? (HALF ? 0x3F000000u : 0x3F800000u) : bits;
-  bits = (m & (1u << (8 + j))) ? (HALF ? 0xBF000000u : 0xBF800000u) : bits;
-  bits = (m & (1u << (16 + j))) ? (HALF ? 0x3F800000u : 0x40000000u) : bits;
-  bits = (m & (1u << (24 + j))) ? (HALF ? 0xBF800000u : 0xC0000000u) : bits;
-  return __uint_as_float(bits);
-}
-
-template <int L, bool HALF = false, bool SKIP0 = false>
-__device__ __forceinline__ void masked_sum_f(uint32_t m, const float (*k)[3], float *out) {
-  float x = 0.0f, y = 0.0f, z = 0.0f;
-#pragma unroll
-  for (int j = 0; j < L; ++j) {
-    const float c = mask_coef_f<HALF>(m, j);
-    if (SKIP0 && c == 0.0f) continue;
-    x = fmaf(c, k[j][0], x);
-    y = fmaf(c, k[j][1], y);
-    z = fmaf(c, k[j][2], z);
-  }
-  out[0] = x;
-  out[1] = y;
-  out[2] = z;
 }
 
 // Per-sample integrand with fp32 arithmetic after the (fp64) VEGAS map; the
@@ -1176,8 +1143,8 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
       kv[1] = k[l][1];
       kv[2] = k[l][2];
     } else {
-      if constexpr (TD) table_sum_f<L>(D->coef_f[l], k, kv);
-      else masked_sum_f<L, false, FixedMasks<ORDER, V>::kFixed>(lmask_of<ORDER, V>(D, l), k, kv);
+      if constexpr (TD) table_sum<L, float>(D->coef_f[l], k, kv);
+      else masked_sum<L, FixedMasks<ORDER, V>::kFixed, float>(lmask_of<ORDER, V>(D, l), k, kv);
     }
     const float k2 = l < L ? r2[l < L ? l : 0]
                            : kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
@@ -1208,82 +1175,50 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   }
   if constexpr (SCR) return 1.0;
 
+  const bool rel = T->rel_target > 0.0;  // uniform
   float dprod = 1.0f;
-  float kcut = 0.0f;  // sum of the cuts' condition numbers (sum |eps|) / |D|
+  float kcut = 0.0f;  // (rel) sum of the cuts' condition numbers (sum |eps|) / |D|
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const uint32_t hm = cut_hole_of<ORDER, V>(D, c), pm = cut_part_of<ORDER, V>(D, c);
     float Dc = 0.0f, Dabs = 0.0f;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      uint32_t bits = (hm & (1u << l)) ? 0x3F800000u : 0u;
-      bits = (pm & (1u << l)) ? 0xBF800000u : bits;
-      const float cf = __uint_as_float(bits);
-      Dc = fmaf(cf, eps[l], Dc);
-      Dabs = fmaf(fabsf(cf), eps[l], Dabs);
+      if constexpr (FixedMasks<ORDER, V>::kFixed) {
+        if (hm & (1u << l)) Dc += eps[l];
+        else if (pm & (1u << l)) Dc -= eps[l];
+        if ((hm | pm) & (1u << l)) Dabs += eps[l];
+      } else {
+        uint32_t bits = (hm & (1u << l)) ? 0x3F800000u : 0u;
+        bits = (pm & (1u << l)) ? 0xBF800000u : bits;
+        const float cf = __uint_as_float(bits);
+        Dc = fmaf(cf, eps[l], Dc);
+        Dabs = fmaf(fabsf(cf), eps[l], Dabs);
+      }
     }
     near |= fabsf(Dc) < bandd * Dabs;
-    kcut = fmaf(Dabs, __builtin_amdgcn_rcpf(fabsf(Dc)), kcut);
+    if (rel) kcut = fmaf(Dabs, __builtin_amdgcn_rcpf(fabsf(Dc)), kcut);
     dprod *= Dc;
   }
 
-  constexpr int NR = 2 * ORDER + 1;
-  float den[NR];
-  float yreg = 0.0f;  // sum of the regulator exponents
-  float yscale[ORDER];  // |p|^2 + |p'|^2 + 2 |p.p'| + m^2: scale of the Yukawa denominators
-  const float m2 = static_cast<float>(a.phys.m2);
-#pragma unroll
-  for (int v = 0; v < ORDER; ++v) {
-    float p[3], q[3];
-    if constexpr (TD) {
-      table_sum_f<L>(D->coef_f[2 * ORDER + 2 * v], k, p);
-      table_sum_f<L>(D->coef_f[2 * ORDER + 2 * v + 1], k, q);
-    } else {
-      masked_sum_f<L, true, FixedMasks<ORDER, V>::kFixed>(pmask_of<ORDER, V>(D, v), k, p);
-      masked_sum_f<L, true, FixedMasks<ORDER, V>::kFixed>(qmask_of<ORDER, V>(D, v), k, q);
-    }
-    const float p2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
-    const float q2 = q[0] * q[0] + q[1] * q[1] + q[2] * q[2];
-    const float pq = p[0] * q[0] + p[1] * q[1] + p[2] * q[2];
-    const float pn = reg_pow<HE>(p2, a.phys.half_exp), qn = reg_pow<HE>(q2, a.phys.half_exp);
-    yreg = v == 0 ? pn + qn : yreg + (pn + qn);
-    const float s2 = p2 + q2 + m2;
-    den[2 * v] = s2 - 2.0f * pq;
-    den[2 * v + 1] = s2 + 2.0f * pq;
-    yscale[v] = s2 + 2.0f * fabsf(pq);
-  }
-  den[NR - 1] = dprod;
-  float pre[NR];
-  pre[0] = den[0];
-#pragma unroll
-  for (int i = 1; i < NR; ++i) pre[i] = pre[i - 1] * den[i];
-  const float yexp = yreg * static_cast<float>(a.phys.invLn);
-  near |= !(fabsf(pre[NR - 1]) > 1e-30f && fabsf(pre[NR - 1]) < 1e30f) || yexp > 80.0f;
+  const float V0 = static_cast<float>(a.phys.V0 / a.phys.vscale);
+  const float Vy = static_cast<float>(a.phys.Vy / a.phys.vscale);
+  float Vd[ORDER], Ve[ORDER], den, yreg, ky = 0.0f;
+  vertex_terms<ORDER, V, HE, TD, CY, true, float>(a, D, k, V0, Vy, Vd, Ve, den, yreg, rel, &ky);
+  const float yexp = yreg * static_cast<float>(a.phys.invLn * a.phys.quarter_n);
+  const float dall = den * dprod;
+  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || yexp > 80.0f;
   if (near) {
     fallback = true;
     return 0.0;
   }
-  float inv = __builtin_amdgcn_rcpf(pre[NR - 1]);
-  inv = inv * (2.0f - pre[NR - 1] * inv);  // one Newton step
-  float rinv[NR];
-#pragma unroll
-  for (int i = NR - 1; i > 0; --i) {
-    rinv[i] = inv * pre[i - 1];
-    inv *= den[i];
-  }
-  rinv[0] = inv;
-  const float V0 = static_cast<float>(a.phys.V0), Vy = static_cast<float>(a.phys.Vy);
-  float Vd[ORDER], Ve[ORDER];
-#pragma unroll
-  for (int v = 0; v < ORDER; ++v) {
-    Vd[v] = fmaf(Vy, rinv[2 * v], V0);
-    Ve[v] = fmaf(Vy, rinv[2 * v + 1], V0);
-  }
+  float inv = __builtin_amdgcn_rcpf(dall);
+  inv = inv * (2.0f - dall * inv);  // one Newton step
   const float regall = __expf(-yexp);
 
   float acc;
   const uint32_t nterms0 = nterms;
-  if (T->rel_target > 0.0) {
+  if (rel) {
     // relative-accuracy target per value: a first-order bound on the fp32
     // evaluation's relative error, in units of the fp32 rounding unit u:
     // the regulator exponent (its momenta carry a few u each), the cuts'
@@ -1297,10 +1232,6 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
       acc = label_sum<ORDER, Q, float, false, X, V, true>(a, D, Vd, Ve, okN, okP, lmask, nterms,
                                                           nullptr, nullptr, &aabs);
     }
-    float ky = 0.0f;
-#pragma unroll
-    for (int v = 0; v < ORDER; ++v)
-      ky = fmaf(yscale[v], rinv[2 * v] + rinv[2 * v + 1], ky);
     const float cancel = aabs * __builtin_amdgcn_rcpf(fabsf(acc));
     const float bound =
         0x1p-24f * (8.0f * yexp + 4.0f * kcut + 4.0f * ky + 8.0f * cancel + 64.0f);
@@ -1319,8 +1250,10 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
     }
   }
   ++npass;
-  return D->pref * static_cast<double>(regall) * static_cast<double>(acc) *
-         static_cast<double>(rinv[NR - 1]);
+  double vs = a.phys.vscale;  // vscale^n (uniform)
+#pragma unroll
+  for (int v = 1; v < ORDER; ++v) vs *= a.phys.vscale;
+  return (D->pref * vs) * static_cast<double>(regall) * static_cast<double>(acc * inv);
 }
 
 template <int ORDER, int Q, bool G, bool X, int V, int HE = 0, bool SCR = false, bool TD = false>
@@ -1384,16 +1317,6 @@ template <int P>
 constexpr bool az_steps() {
   return prec_of<P>() != 1;
 }
-// Per-vertex-pair inversion (see diag_weight64) where the registers it frees
-// give the kernel one more wave per SIMD: the third-order fp32 kernels (their
-// fp64 re-evaluation path) fit in 168 VGPRs with it (3 waves instead of 2).
-// Elsewhere the prefix form, which issues fewer instructions, at the same
-// occupancy.
-template <int ORDER, int Q, int P>
-constexpr bool pair_inv() {
-  return ORDER == 3 && prec_of<P>() == 1;
-}
-
 template <int ORDER, int Q, int P, bool X, int HE>
 __device__ __forceinline__ double eval_sample(const KArgs &a, const TaskDev *__restrict__ T,
                                               const DiagDev *__restrict__ D,
@@ -1402,21 +1325,20 @@ __device__ __forceinline__ double eval_sample(const KArgs &a, const TaskDev *__r
                                               uint32_t &nterms, uint32_t &nfb) {
   constexpr int PP = prec_of<P>();
   constexpr bool G = group_of<P>();
-  constexpr bool PI = pair_inv<ORDER, Q, P>();
   double w = 0.0;
   with_variant<ORDER, G, cycle_form<ORDER, Q, G, X, PP == 2>()>(D, [&](auto vt) {
     constexpr int V = decltype(vt)::value;
     constexpr bool AZ = az_steps<P>();
     const double jc = jac_const<ORDER, AZ>(a, T);
     if (PP != 1) {
-      w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, PP == 2, G, X, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
       return;
     }
     bool fb = false;
     w = eval_fp32<ORDER, Q, G, X, V, HE>(a, T, D, Ls, jc, s, iter, bins, npass, nterms, fb);
     if (fb) {
       ++nfb;
-      w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, false, G, X, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
     }
   });
   return w;
@@ -1620,7 +1542,6 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
   };
   constexpr int PP = prec_of<P>();
   constexpr bool G = group_of<P>();
-  constexpr bool PI = pair_inv<ORDER, Q, P>();
   constexpr bool SCR = screen_on<ORDER, Q, P, X>();
   const int lane = tid & 63;
   // per wavefront: the fp64 re-evaluation queue, then the Pauli screen's
@@ -1639,7 +1560,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         if (lane < take) {
           const uint64_t s = base + pqueue[lane];
           int bins[ND];
-          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD, AZ>(
+          const double w = eval_fp64<ORDER, Q, false, G, X, V, false, HE, false, TD, AZ>(
               a, T, D, Ls, jc, s, iter, bins, npass, nterms);
           accumulate(w, bins);
         }
@@ -1650,7 +1571,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         bool go = false;
         if (s < N) {
           int bins[ND];
-          go = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, true, TD, AZ>(
+          go = eval_fp64<ORDER, Q, false, G, X, V, false, HE, true, TD, AZ>(
                    a, T, D, Ls, jc, s, iter, bins, npass, nterms) != 0.0;
           if (!go) accumulate_zero();
         }
@@ -1665,7 +1586,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
           int bins[ND];
           if constexpr (R) {
             double wr[kMaxReg];
-            const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, true, HE, false, TD, AZ>(
+            const double w = eval_fp64<ORDER, Q, false, G, X, V, true, HE, false, TD, AZ>(
                 a, T, D, Ls, jc, s, iter, bins, npass, nterms, wr);
             accumulate(w, bins);
             // the extrapolation's weights sum to one, so its shifted value
@@ -1681,7 +1602,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
             rs[2 * kMaxReg] += dx;
             rs[2 * kMaxReg + 1] += dx * dx;
           } else {
-            const double w = eval_fp64<ORDER, Q, PP == 2, G, X, PI, V, false, HE, false, TD, AZ>(
+            const double w = eval_fp64<ORDER, Q, PP == 2, G, X, V, false, HE, false, TD, AZ>(
                 a, T, D, Ls, jc, s, iter, bins, npass, nterms);
             accumulate(w, bins);
           }
@@ -1696,7 +1617,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         if (lane < take) {
           const uint64_t s = base + queue[lane];
           int bins[ND];
-          const double w = eval_fp64<ORDER, Q, false, G, X, PI, V, false, HE, false, TD, AZ>(
+          const double w = eval_fp64<ORDER, Q, false, G, X, V, false, HE, false, TD, AZ>(
               a, T, D, Ls, jc, s, iter, bins, npass, nterms);
           accumulate(w, bins);
         }
@@ -1991,7 +1912,6 @@ __global__ __launch_bounds__(256) void dump_samples(KArgs a, int t, uint32_t ite
                                                    uint64_t count, double *out, double *out_reg) {
   extern __shared__ double smem[];
   constexpr int ND = 3 * (ORDER + 1);
-  constexpr bool PI = pair_inv<ORDER, Q, P>();
   const TaskDev *T = a.tasks + t;
   const DiagDev *D = a.diags + T->diag;
   const int nb = a.phys.nb;
@@ -2019,7 +1939,7 @@ __global__ __launch_bounds__(256) void dump_samples(KArgs a, int t, uint32_t ite
       with_variant<ORDER, group_of<P>(), cycle_form<ORDER, Q, group_of<P>(), X, false>()>(
           D, [&](auto vt) {
         constexpr int V = decltype(vt)::value;
-        out[i] = eval_fp64<ORDER, Q, false, group_of<P>(), X, PI, V, true, HE>(
+        out[i] = eval_fp64<ORDER, Q, false, group_of<P>(), X, V, true, HE>(
             a, T, D, Ls, jac_const<ORDER, true>(a, T), first + i, iter, bins, np, nt, wr);
       });
       if (out_reg)

@@ -301,9 +301,8 @@ void fill_diag_dev(const Diagram &d, DiagDev &dd, bool canonical) {
       if (d.cut[c][l] > 0) dd.cut_hole[c] |= 1u << sl;
       if (d.cut[c][l] < 0) dd.cut_part[c] |= 1u << sl;
     }
-  // the masks decoded: bit j +1, 8 + j -1, 16 + j +2, 24 + j -2 (halved
-  // for the vertex sums)
-  auto unpack = [&](uint32_t m, double scale, int s) {
+  // the masks decoded: bit j +1, 8 + j -1, 16 + j +2, 24 + j -2
+  auto unpack = [&](uint32_t m, int s) {
     for (int j = 0; j < kDescCoefStride; ++j) {
       double c = 0.0;
       if (j < 8) {
@@ -312,17 +311,17 @@ void fill_diag_dev(const Diagram &d, DiagDev &dd, bool canonical) {
         if (m & (1u << (16 + j))) c = 2.0;
         if (m & (1u << (24 + j))) c = -2.0;
       }
-      dd.coef_d[s][j] = c * scale;
-      dd.coef_f[s][j] = static_cast<float>(c * scale);
+      dd.coef_d[s][j] = c;
+      dd.coef_f[s][j] = static_cast<float>(c);
     }
   };
   for (int s = 0; s < kDescCoefSums; ++s)
     for (int j = 0; j < kDescCoefStride; ++j) dd.coef_d[s][j] = dd.coef_f[s][j] = 0;
   const int nl = 2 * d.order;
-  for (int sl = 0; sl < nl && sl < d.nlines; ++sl) unpack(dd.lmask[sl], 1.0, sl);
+  for (int sl = 0; sl < nl && sl < d.nlines; ++sl) unpack(dd.lmask[sl], sl);
   for (int v = 0; v < d.order; ++v) {
-    unpack(dd.pmask_v[v], 0.5, nl + 2 * v);
-    unpack(dd.qmask_v[v], 0.5, nl + 2 * v + 1);
+    unpack(dd.pmask_v[v], nl + 2 * v);
+    unpack(dd.qmask_v[v], nl + 2 * v + 1);
   }
 }
 
@@ -740,6 +739,23 @@ Layout layout_of(const mbpt_task_set *set, uint64_t max_samples, int max_iters, 
   return L;
 }
 
+Phys phys_of(const mbpt_context *ctx) {
+  const mbpt_interaction &v = ctx->v;
+  Phys p{};
+  p.V0 = v.C0 * v.hbarc;
+  p.Vy = v.Cy * v.hbarc;
+  p.m2 = v.mpi * v.mpi;
+  p.invLn = std::pow(v.Lambda, -static_cast<double>(v.reg_exp));
+  p.quarter_n = std::ldexp(1.0, -v.reg_exp);
+  p.vscale = std::fabs(p.V0) + std::fabs(p.Vy) / p.m2;
+  if (!(p.vscale > 0.0)) p.vscale = 1.0;
+  p.hb2m = 0.5 * v.hbar2_m;
+  p.half_exp = v.reg_exp / 2;
+  p.nb = ctx->desc.n_bins;
+  p.seed = ctx->desc.seed;
+  return p;
+}
+
 KArgs kargs_of(const mbpt_task_set *set) {
   const mbpt_context *ctx = set->ctx;
   KArgs a{};
@@ -765,15 +781,7 @@ KArgs kargs_of(const mbpt_task_set *set) {
   a.total_items = 0;
   a.spt = set->spt;
   a.label_mode = ctx->desc.label_mode;
-  const mbpt_interaction &v = ctx->v;
-  a.phys.V0 = v.C0 * v.hbarc;
-  a.phys.Vy = v.Cy * v.hbarc;
-  a.phys.m2 = v.mpi * v.mpi;
-  a.phys.invLn = std::pow(v.Lambda, -static_cast<double>(v.reg_exp));
-  a.phys.hb2m = 0.5 * v.hbar2_m;
-  a.phys.half_exp = v.reg_exp / 2;
-  a.phys.nb = ctx->desc.n_bins;
-  a.phys.seed = ctx->desc.seed;
+  a.phys = phys_of(ctx);
   a.phys.spectrum = ctx->desc.spectrum;
   return a;
 }

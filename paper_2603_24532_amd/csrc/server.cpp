@@ -282,15 +282,7 @@ KArgs server_kargs(const mbpt_server *s) {
   a.ntasks = s->max_slots;
   a.spt = s->spt;
   a.label_mode = ctx->desc.label_mode;
-  const mbpt_interaction &v = ctx->v;
-  a.phys.V0 = v.C0 * v.hbarc;
-  a.phys.Vy = v.Cy * v.hbarc;
-  a.phys.m2 = v.mpi * v.mpi;
-  a.phys.invLn = std::pow(v.Lambda, -static_cast<double>(v.reg_exp));
-  a.phys.hb2m = 0.5 * v.hbar2_m;
-  a.phys.half_exp = v.reg_exp / 2;
-  a.phys.nb = ctx->desc.n_bins;
-  a.phys.seed = ctx->desc.seed;
+  a.phys = phys_of(ctx);
   a.phys.spectrum = MBPT_SPECTRUM_FREE;
   return a;
 }
