@@ -410,7 +410,7 @@ size_t sample_lds_bytes(int nd, int nb, int block, int ntab) {
   // per wavefront each)
   return fixed_lds_bytes() + hf_lds_doubles(ntab) * sizeof(double) +
          (3 * static_cast<size_t>(nd) * nb + 6 * (block / 64)) * sizeof(double) +
-         (block / 64) * 256 * sizeof(uint32_t);
+         (block / 64) * 256 * sizeof(uint32_t) + 16;  // + alignment of the label tables
 }
 
 // Dispatch on (order, q) to the launchers of kernels_inst.hip.

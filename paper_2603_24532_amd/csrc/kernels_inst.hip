@@ -58,7 +58,7 @@ hipError_t launch_order_oq<O, Q>(const KArgs &a, int prec, bool group, int k0, i
       return launch_o4_fixed<P>(a, k0, k1, grid, block, st);
     } else {
       const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
-                         cycle_lds_bytes<O, Q, P, X>();
+                         label_lds_bytes<O, Q, P, X>();
       hipLaunchKernelGGL((sample_order<O, Q, P, X, HE>), dim3(grid), dim3(block), lds, st, a, k0,
                          k1);
       return hipGetLastError();
@@ -75,7 +75,7 @@ hipError_t launch_persist_oq<O, Q>(const KArgs &a, int prec, bool group, int k0,
     constexpr bool X = decltype(x)::value;
     constexpr int HE = decltype(h)::value;
     const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
-                       cycle_lds_bytes<O, Q, P, X>();
+                       label_lds_bytes<O, Q, P, X>();
     auto kern = sample_persistent<O, Q, P, X, HE>;
     // more blocks than can be resident: the extra ones start as others
     // finish and find the counter exhausted, so the device stays full
@@ -103,7 +103,7 @@ hipError_t launch_dump_oq<O, Q>(const KArgs &a, int t, int prec, bool group, uin
     const dim3 grid(static_cast<unsigned>((count + block - 1) / block));
     const size_t lds = fixed_lds_bytes() + hf_lds_doubles(lds_tables<Q, P>()) * sizeof(double) +
                        2 * static_cast<size_t>(3 * (O + 1)) * a.phys.nb * sizeof(double) +
-                       cycle_lds_bytes<O, Q, P, X>();
+                       label_lds_bytes<O, Q, P, X>();
     hipLaunchKernelGGL((dump_samples<O, Q, P, X, HE>), grid, dim3(block), lds, st, a, t, iter,
                        first, count, out, out_reg);
     return hipGetLastError();
