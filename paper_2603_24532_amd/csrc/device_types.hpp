@@ -193,8 +193,8 @@ struct Phys {
   double m2;        // mpi^2
   double invLn;     // Lambda^{-reg_exp}
   double quarter_n; // 4^{-reg_exp / 2}: (2p)^n to p^n
-  double vscale;    // scale of the interaction, |V0| + |Vy| / m2 (1 if that is 0)
-  double hb2m;      // hbar^2 / 2m
+  double vscale;    // V0 or Vy, the larger (1 if both are 0): the fp32 vertices' scale
+  double hb2m, inv_hb2m;  // hbar^2 / 2m and its reciprocal
   int half_exp;     // reg_exp / 2
   int nb;           // bins per dimension
   uint32_t seed;

@@ -470,13 +470,15 @@ __device__ __forceinline__ double sqrt_normal(double a) {
   return fma(d, h, g);
 }
 
-// The same in fp32 (rsq, then one Newton correction: within an ulp of the
-// root), a clamped to 1e-30.
-__device__ __forceinline__ float sqrt_normal_f(float a) {
+// sin theta from its square a in fp32: rsq, then one Newton correction (within
+// an ulp of the root), a clamped to 1e-30.  The hardware sine and cosine of the
+// azimuth come out short, s^2 + c^2 = 1 - 6.5e-8 on average; the correction
+// makes up for that, so the squared momenta are not all too small.
+__device__ __forceinline__ float sin_theta_f(float a) {
   a = fmaxf(a, 1e-30f);
   const float y = __builtin_amdgcn_rsqf(a);
   const float g = a * y;
-  return fmaf(fmaf(-g, g, a), 0.5f * y, g);
+  return fmaf(fmaf(a, 6.5e-8f, fmaf(-g, g, a)), 0.5f * y, g);
 }
 
 // 1/d from the hardware reciprocal and two Newton steps (d normal and finite;
@@ -506,8 +508,8 @@ __device__ __forceinline__ void pair_merge(double &s, double &c, double s2, doub
 // in turn): with the bin's lower edge e, width w and a random word's fraction
 // r = (f + 1/2) 2^-32, f whole, the mapped coordinate x = e + r w is one fma of
 // f with the pair, scaled to what the loop momentum is built from: the radius
-// R x0, the cosine 2 x1 - 1, and the azimuth in turns, or (AZ) in table steps
-// of the turn.  Scaling here, once per work item, takes a multiplication per
+// R x0, the cosine 2 x1 - 1, and the azimuth in table steps of the turn (AZ),
+// or in turns from -1/2 to 1/2 (fp32: half the rounding of 0 to 1).  Scaling here, once per work item, takes a multiplication per
 // coordinate and the fraction's conversion to [0, 1) out of every sample; on
 // MI355X (with the one-product bin split of vegas_map and the short fp32 root)
 // orders 2+3, 36 tasks x 2^24 fp32, 7.67 -> 6.95 ms per iteration, and the 585
@@ -520,7 +522,7 @@ __device__ __forceinline__ double2 grid_pair(int m, double e0, double e1, double
   const int role = m % 3;
   if (role == 0) return make_double2(R * e, R * ws);
   if (role == 1) return make_double2(fma(2.0, e, -1.0), 2.0 * ws);
-  return AZ ? make_double2(MBPT_TURN_STEPS * e, MBPT_TURN_STEPS * ws) : make_double2(e, ws);
+  return AZ ? make_double2(MBPT_TURN_STEPS * e, MBPT_TURN_STEPS * ws) : make_double2(e - 0.5, ws);
 }
 
 // Radius of the sphere loop j of the task's first descriptor D is drawn from.
@@ -594,7 +596,7 @@ __device__ __forceinline__ double loop_momenta(const KArgs &a, const TaskDev *__
     const double rad = x[3 * j], ct = x[3 * j + 1];
     const double st = sqrt_normal((1.0 - ct) * (1.0 + ct));
     double sp, cp;
-    sincos_turn(Ls.turn, AZ ? x[3 * j + 2] : x[3 * j + 2] * MBPT_TURN_STEPS, sp, cp);
+    sincos_turn(Ls.turn, AZ ? x[3 * j + 2] : (x[3 * j + 2] + 0.5) * MBPT_TURN_STEPS, sp, cp);
     const double rs = rad * st;
     k[j][0] = rs * cp;
     k[j][1] = rs * sp;
@@ -616,9 +618,9 @@ __device__ __forceinline__ double loop_momenta(const KArgs &a, const TaskDev *__
 #pragma unroll
   for (int j = 0; j < L; ++j) {
     const float rad = static_cast<float>(x[3 * j]), ct = static_cast<float>(x[3 * j + 1]);
-    const float st = sqrt_normal_f((1.0f - ct) * (1.0f + ct));
+    const float st = sin_theta_f((1.0f - ct) * (1.0f + ct));
     const float rev = static_cast<float>(x[3 * j + 2]);
-    const float rs = rad * st;
+    const float rs = -rad * st;  // half a turn from rev to the azimuth
     k[j][0] = rs * __builtin_amdgcn_cosf(rev);
     k[j][1] = rs * __builtin_amdgcn_sinf(rev);
     k[j][2] = rad * ct;
@@ -1060,7 +1062,7 @@ __device__ __forceinline__ double exp_nonpos(double x, const double *ex) {
 // iteration of 2^21 samples on MI355X, orders 2+3 fp32 6.95 -> 6.73 ms).  The
 // regulators come out too, as exp(-yreg), yreg = 4^n sum_v (p^n + p'^n) (n the
 // regulator exponent).  V0, Vy: the interaction, in fp32 divided by
-// Phys::vscale, so |Vd|, |Ve| <= dd de.  KY: *ky adds the Yukawa denominators'
+// Phys::vscale, so that one of them is 1 and the other at most 1.  KY: *ky adds the Yukawa denominators'
 // condition numbers (s + 2 |p.p'|)(1 / dd + 1 / de), if rel (uniform).
 template <int ORDER, int V, int HE, bool TD, bool NEG, bool KY, typename F>
 __device__ __forceinline__ void vertex_terms(const KArgs &a, const DiagDev *__restrict__ D,
@@ -1098,6 +1100,16 @@ __device__ __forceinline__ void vertex_terms(const KArgs &a, const DiagDev *__re
   }
 }
 
+// (hbar^2 / 2m)^-NC, the unit of 1 / prod_c D_c with the denominators formed from
+// the squared momenta (uniform).
+template <int NC>
+__device__ __forceinline__ double energy_unit(const KArgs &a) {
+  double u = 1.0;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) u *= a.phys.inv_hb2m;
+  return u;
+}
+
 // Contribution of one diagram at the loop momenta k (prefactor, regulators,
 // label sum and denominators; without the Jacobian and 1/n).  HF: single-
 // particle energies of the Hartree-Fock spectrum (tables in LDS).
@@ -1132,9 +1144,11 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     // (a loop line's k^2 is its squared radius)
     const double k2 = l < L ? r2[l < L ? l : 0]
                             : kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
-    eps[l] = a.phys.hb2m * k2;
+    // the free spectrum's energies in units of hbar^2 / 2m (energy_unit)
+    eps[l] = k2;
     deps[l] = 0.0;
     if constexpr (HF) {
+      eps[l] = a.phys.hb2m * k2;
       const double kk = sqrt_normal(k2);
       const double sn = hf_sigma(Ls.hf, 0, kk, T->hf_inv_h);
       if (Q == 4) deps[l] = hf_sigma(Ls.hf, 1, kk, T->hf_inv_h) - sn;
@@ -1190,10 +1204,11 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     acc = label_sum<ORDER, Q, double, iso_den, X, V>(a, D, Vd, Ve, okN, okP, lmask, nterms, Dn,
                                                      deps);
   }
+  const double pref = D->pref * (HF ? 1.0 : energy_unit<NC>(a));
   if constexpr (REG) {
-    const double base = D->pref * regall * acc * rcp_newton(den);
+    const double base = pref * regall * acc * rcp_newton(den);
     for (int r = 0; r < a.nreg; ++r) {
-      const double eta = (r + 1) * a.reg_eta;
+      const double eta = (r + 1) * (a.reg_eta / a.phys.hb2m);
       double pk = 1.0;
 #pragma unroll
       for (int c = 0; c < NC; ++c) pk *= Dn[c] - eta;
@@ -1202,7 +1217,7 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     return base * rcp_newton(dprod);
   }
   // (with isospin-dependent energies the label sum holds the denominators)
-  return D->pref * regall * acc * rcp_newton(iso_den ? den : den * dprod);
+  return pref * regall * acc * rcp_newton(iso_den ? den : den * dprod);
 }
 
 // One sample of a task: VEGAS map, loop momenta (radii from the first
@@ -1272,7 +1287,6 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   constexpr int NC = ORDER - 1;
   const float kFn2 = static_cast<float>(T->kF2[0]), kFp2 = static_cast<float>(T->kF2[1]);
   const float bandk = static_cast<float>(T->band_k), bandd = static_cast<float>(T->band_d);
-  const float hb2m = static_cast<float>(a.phys.hb2m);
   float eps[NL];
   uint32_t inN = 0, inP = 0;
   float nearN = 3e38f, nearP = 3e38f;  // smallest distance to a Fermi surface
@@ -1287,9 +1301,12 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
       if constexpr (TD) table_sum<L, float>(D->coef_f[l], k, kv);
       else masked_sum<L, FixedMasks<ORDER, V>::kFixed, float>(lmask_of<ORDER, V>(D, l), k, kv);
     }
-    const float k2 = l < L ? r2[l < L ? l : 0]
-                           : kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
-    eps[l] = hb2m * k2;
+    // the Pauli tests take a loop line's squared radius; the energies take the
+    // components, as the other lines do, so that the denominators' small
+    // differences see one and the same set of momenta
+    const float kk = kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2];
+    const float k2 = l < L ? r2[l < L ? l : 0] : kk;
+    eps[l] = kk;  // in units of hbar^2 / 2m (energy_unit)
     const float tN = k2 - kFn2;
     nearN = fminf(nearN, fabsf(tN));
     inN = push_sign(inN, tN);
@@ -1342,23 +1359,30 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   const float Vy = static_cast<float>(a.phys.Vy / a.phys.vscale);
   float Vd[ORDER], Ve[ORDER], den, yreg, ky = 0.0f;
   vertex_terms<ORDER, V, HE, TD, LF != kConfigs, true, float>(a, D, k, V0, Vy, Vd, Ve, den, yreg, rel, &ky);
-  const float yexp = yreg * static_cast<float>(a.phys.invLn * a.phys.quarter_n);
+  // regulator exponent in powers of two, yreg times a constant in two parts:
+  // one float's rounding of it alone moved every weight the same way (1.3e-7
+  // on average at exponents up to 20)
+  const double ylog2 = a.phys.invLn * a.phys.quarter_n * 1.4426950408889634;
+  const float yhi = static_cast<float>(ylog2), ylo = static_cast<float>(ylog2 - yhi);
+  const float y2 = yreg * yhi;
+  const float yres = fmaf(yreg, ylo, fmaf(yreg, yhi, -y2));
   const float dall = den * dprod;
-  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || yexp > 80.0f;
+  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || y2 > 115.0f;
   if (near) {
     fallback = true;
     return 0.0;
   }
   float inv = __builtin_amdgcn_rcpf(dall);
-  inv = inv * (2.0f - dall * inv);  // one Newton step
-  const float regall = __expf(-yexp);
+  inv = fmaf(inv, fmaf(-dall, inv, 1.0f), inv);  // one Newton step
+  const float rexp = __builtin_amdgcn_exp2f(-y2);
+  const float regall = fmaf(rexp, -0.693147181f * yres, rexp);
 
   float acc;
   const uint32_t nterms0 = nterms;
   if (rel) {
     // relative-accuracy target per value: a first-order bound on the fp32
     // evaluation's relative error, in units of the fp32 rounding unit u:
-    // the regulator exponent (its momenta carry a few u each), the cuts'
+    // eight times the regulator exponent (its momenta carry a few u each), the cuts'
     // and the Yukawa denominators' condition numbers, the label sum's
     // cancellation (sum of |terms| / |sum|) and a constant for the rest
     float aabs;
@@ -1373,8 +1397,13 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
                                                           nullptr, nullptr, &aabs);
     }
     const float cancel = aabs * __builtin_amdgcn_rcpf(fabsf(acc));
+    if (!(fabsf(acc) < 3e38f)) {  // out of the fp32 range
+      nterms = nterms0;
+      fallback = true;
+      return 0.0;
+    }
     const float bound =
-        0x1p-24f * (8.0f * yexp + 4.0f * kcut + 4.0f * ky + 8.0f * cancel + 64.0f);
+        0x1p-24f * (5.5451774f * y2 + 4.0f * kcut + 4.0f * ky + 8.0f * cancel + 64.0f);
     if (!(bound <= static_cast<float>(T->rel_target))) {
       nterms = nterms0;
       fallback = true;
@@ -1389,12 +1418,18 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
       acc = label_sum<ORDER, Q, float, false, X, V>(a, D, Vd, Ve, okN, okP, lmask, nterms,
                                                    nullptr, nullptr);
     }
+    if (!(fabsf(acc) < 3e38f)) {  // out of the fp32 range
+      nterms = nterms0;
+      fallback = true;
+      return 0.0;
+    }
   }
   ++npass;
-  double vs = a.phys.vscale;  // vscale^n (uniform)
+  double unit = energy_unit<NC>(a);  // times vscale^n (uniform)
 #pragma unroll
-  for (int v = 1; v < ORDER; ++v) vs *= a.phys.vscale;
-  return (D->pref * vs) * static_cast<double>(regall) * static_cast<double>(acc * inv);
+  for (int v = 0; v < ORDER; ++v) unit *= a.phys.vscale;
+  return (D->pref * unit) * static_cast<double>(regall) * static_cast<double>(acc) *
+         static_cast<double>(inv);
 }
 
 template <int ORDER, int Q, bool G, bool X, int V, int HE = 0, bool SCR = false, bool TD = false>

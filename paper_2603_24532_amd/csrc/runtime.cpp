@@ -747,9 +747,10 @@ Phys phys_of(const mbpt_context *ctx) {
   p.m2 = v.mpi * v.mpi;
   p.invLn = std::pow(v.Lambda, -static_cast<double>(v.reg_exp));
   p.quarter_n = std::ldexp(1.0, -v.reg_exp);
-  p.vscale = std::fabs(p.V0) + std::fabs(p.Vy) / p.m2;
-  if (!(p.vscale > 0.0)) p.vscale = 1.0;
+  p.vscale = std::fabs(p.V0) >= std::fabs(p.Vy) ? p.V0 : p.Vy;
+  if (p.vscale == 0.0) p.vscale = 1.0;
   p.hb2m = 0.5 * v.hbar2_m;
+  p.inv_hb2m = 1.0 / p.hb2m;
   p.half_exp = v.reg_exp / 2;
   p.nb = ctx->desc.n_bins;
   p.seed = ctx->desc.seed;
