@@ -445,9 +445,9 @@ int mbpt_set_grid(mbpt_task_set *set, int task, const double *edges_host);
 int mbpt_autotune(mbpt_task_set *set, uint64_t samples_per_iter, int *threads_per_block,
                   int *samples_per_thread, double *ms_per_iter);
 
-/* Timing of the sample kernels since the last call (HIP events on the
- * context stream): launches, total kernel milliseconds, samples evaluated,
- * and algorithmic FLOPs per evaluation counted from the descriptors (FMA = 2,
+/* Timing of the sample kernels since the last call (by the device clock, up
+ * to each iteration end): launches,
+ * total kernel milliseconds, samples evaluated, and algorithmic FLOPs per evaluation counted from the descriptors (FMA = 2,
  * add/mul = 1, each exp/sqrt/sincos/division = 1). */
 int mbpt_kernel_stats(mbpt_context *ctx, uint64_t *launches, double *kernel_ms,
                       uint64_t *evals, double *flops);

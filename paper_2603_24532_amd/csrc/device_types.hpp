@@ -229,7 +229,7 @@ constexpr int kFinishThreads = 1024;
 constexpr int kFinishBatch = 4;
 
 // One task: parameters (host-written) and running state (device-written).
-struct alignas(16) TaskDev {
+struct alignas(16) TaskParams {
   int diag, nd, grid_off, hist_off;
   int item_begin, nitems, res_off, res_cap;  // work items [item_begin, +nitems)
   int store_begin;                           // partials/counters slot of the first item
@@ -247,7 +247,8 @@ struct alignas(16) TaskDev {
   int train_iters;        // > 0: first train_iters iterations are training (see finish_iteration)
   int active;
   int plan;             // iterations of the current launch sequence it takes part in
-  // state (written by the device)
+};
+struct alignas(16) TaskState {
   uint32_t iter;        // Philox iteration word of the next iteration
   int it_done;
   double shift;
@@ -256,7 +257,11 @@ struct alignas(16) TaskDev {
   int ncomb;            // iterations combined into the running sums
   double lastI, lastV;
   uint64_t nevals, nfallback, npass, nterms;
+  // sample-kernel time, kept by task 0 of a launch sequence (device clock
+  // ticks): when the iteration's sample launches could start, total so far
+  uint64_t t_begin, t_busy;
 };
+struct TaskDev : TaskParams, TaskState {};
 
 // Work-item counters of the persistent launches, one per order (index 1..5),
 // and the blocks per compute unit such a launch starts.
@@ -291,6 +296,7 @@ struct KArgs {
   int total_items;
   int spt;                // samples per thread per item
   int label_mode;         // 0 factorised label sums, 1 explicit terms
+  int timed;              // 1: keep the sample-kernel time (TaskState::t_begin, t_busy)
   Phys phys;
 };
 

@@ -30,72 +30,110 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Lepage refinement of one dimension by one wavefront (lanes own bins b and
-// b + 64).  hist: sums of w^2 per bin; edges: nb + 1 edges, rewritten.
+// v of the lane a DPP control selects, 0 where it selects none.
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+// Inclusive prefix sum over the wavefront's 64 lanes: shifts within rows of 16
+// lanes, then the row totals broadcast (DPP moves; the LDS permutes of
+// __shfl_up take several times their latency).
+__device__ __forceinline__ double wave_scan(double v) {
+  v += dpp_or_zero<0x111>(v);        // row_shr:1
+  v += dpp_or_zero<0x112>(v);        // row_shr:2
+  v += dpp_or_zero<0x114>(v);        // row_shr:4
+  v += dpp_or_zero<0x118>(v);        // row_shr:8
+  v += dpp_or_zero<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+// The value of lane 63, in every lane.
+__device__ __forceinline__ double last_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// A dimension's histogram and grid edges as a wavefront's lanes hold them (bins
+// and edges b and b + 64).
+struct DimRegs {
+  double h[2], e[2];
+};
+__device__ __forceinline__ DimRegs load_dim(const double *hist, const double *edges, int nb) {
+  const int lane = threadIdx.x & 63;
+  DimRegs r;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int b = lane + 64 * k;
+    r.h[k] = b < nb ? hist[b] : 0.0;
+    r.e[k] = b < nb ? edges[b] : 0.0;
+  }
+  return r;
+}
+
+// Lepage refinement of one dimension by one wavefront.  in: sums of w^2 per bin
+// and the lower edges; edges: nb + 1 edges, rewritten.
 // Smoothing (7,1)/8, (1,6,1)/8, (1,7)/8, normalisation, compression
 // ((d - 1)/ln d)^alpha, then new edges placing an equal share of the total
 // compressed weight in every new bin (weight uniform inside old bins).
-// scr: 2 nb + 2 doubles of LDS for this wave.
-__device__ void refine_dim_wave(double *hist, double *edges, int nb, double alpha, double *scr) {
+// scr: 3 nb + 3 doubles of LDS for this wave.
+__device__ void refine_dim_wave(const DimRegs &in, double *edges, int nb, double alpha,
+                                double *scr) {
   const int lane = threadIdx.x & 63;
-  double *cum = scr;            // nb + 1 prefix sums of r
-  double *r = scr + nb + 1;     // nb compressed weights
-  double dsv[2] = {0.0, 0.0};
-  double part = 0.0;
+  const int halves = nb > 64 ? 2 : 1;
+  double *hist = scr;               // nb sums, then nb compressed weights
+  double *cum = scr + nb;           // nb + 1 prefix sums of the weights
+  double *old = scr + 2 * nb + 1;   // nb + 1 edges
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int b = lane + 64 * h;
+  for (int k = 0; k < 2; ++k) {
+    const int b = lane + 64 * k;
     if (b < nb) {
-      double d;
-      if (b == 0) d = (7.0 * hist[0] + hist[1]) / 8.0;
-      else if (b == nb - 1) d = (hist[nb - 2] + 7.0 * hist[nb - 1]) / 8.0;
-      else d = (hist[b - 1] + 6.0 * hist[b] + hist[b + 1]) / 8.0;
-      dsv[h] = d;
-      part += d;
+      hist[b] = in.h[k];
+      old[b] = in.e[k];
     }
   }
-  const double sum = wave_sum(part);
-  if (!(sum > 0.0)) return;  // uniform across the wave
-  double rp = 0.0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int b = lane + 64 * h;
-    if (b < nb) {
-      const double v = dsv[h] / sum;
-      double rb;
-      if (v <= 0.0) rb = 0.0;
-      else if (v >= 1.0) rb = 1.0;
-      else rb = pow((v - 1.0) / log(v), alpha);
-      r[b] = rb;
-      rp += rb;
-    }
-  }
-  const double rtot = wave_sum(rp);
-  if (!(rtot > 0.0)) return;
-  __builtin_amdgcn_wave_barrier();
-  // inclusive scan over bins 0..63, then 64..127 offset by the first half
-  double carry = 0.0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int b = lane + 64 * h;
-    double x = (b < nb) ? r[b] : 0.0;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const double y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
-    }
-    if (b < nb) cum[b + 1] = carry + x;
-    carry += __shfl(x, 63, 64);
-  }
-  if (lane == 0) cum[0] = 0.0;
-  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) old[nb] = 1.0;
   __syncwarp();
-  const double per = rtot / nb;
-  double xnew[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int kk = lane + 64 * h;
-    xnew[h] = 0.0;
+  double dsv[2] = {0.0, 0.0};
+  for (int k = 0; k < halves; ++k) {
+    const int b = lane + 64 * k;
+    if (b < nb) {
+      if (b == 0) dsv[k] = (7.0 * hist[0] + hist[1]) / 8.0;
+      else if (b == nb - 1) dsv[k] = (hist[nb - 2] + 7.0 * hist[nb - 1]) / 8.0;
+      else dsv[k] = (hist[b - 1] + 6.0 * hist[b] + hist[b + 1]) / 8.0;
+    }
+  }
+  const double sum = last_lane(wave_scan(dsv[0] + dsv[1]));
+  if (!(sum > 0.0)) return;  // uniform across the wave
+  __syncwarp();
+  double *r = hist;
+  double carry = 0.0;
+  for (int k = 0; k < halves; ++k) {
+    const int b = lane + 64 * k;
+    double rb = 0.0;
+    if (b < nb) {
+      const double v = dsv[k] / sum;
+      if (v <= 0.0) {
+        rb = 0.0;
+      } else if (v >= 1.0) {
+        rb = 1.0;
+      } else {
+        const double c = (v - 1.0) / log(v);
+        rb = alpha == 1.5 ? c * sqrt(c) : pow(c, alpha);  // 1.5: the default
+      }
+      r[b] = rb;
+    }
+    const double x = wave_scan(rb);
+    if (b < nb) cum[b + 1] = carry + x;
+    carry += last_lane(x);
+  }
+  if (!(carry > 0.0)) return;
+  if (lane == 0) cum[0] = 0.0;
+  __syncwarp();
+  const double per = carry / nb;
+  for (int k = 0; k < halves; ++k) {
+    const int kk = lane + 64 * k;
     if (kk >= 1 && kk < nb) {
       const double target = per * kk;
       // smallest j with cum[j + 1] >= target (j = nb - 1 if none)
@@ -108,22 +146,23 @@ __device__ void refine_dim_wave(double *hist, double *edges, int nb, double alph
       const int j = lo;
       double frac = r[j] > 0.0 ? (target - cum[j]) / r[j] : 0.0;
       frac = fmin(1.0, fmax(0.0, frac));
-      xnew[h] = edges[j] + frac * (edges[j + 1] - edges[j]);
+      edges[kk] = old[j] + frac * (old[j + 1] - old[j]);
     }
-  }
-  __syncwarp();
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int kk = lane + 64 * h;
-    if (kk >= 1 && kk < nb) edges[kk] = xnew[h];
   }
 }
 
 // step_iter: index of this iteration within the launch sequence; tasks whose
 // plan ends before it sit this iteration out.
-// One block of kFinishThreads per task: every thread reduces a strided set of
+// One block of kFinishThreads per task.  Every thread reduces a strided set of
 // item partials (loads of kFinishBatch items issued together, merged in item
-// order), then the waves reduce in order and each wave refines dimensions.
+// order); then one thread of the first wave forms the estimate and updates the
+// running state while the other waves refine a dimension each, from a histogram
+// and edges loaded at the start.  The kernel is a latency chain (one block per
+// task, a few hundred values): estimate before refinement, pow and LDS-permute
+// scans in sequence took 12.3 us for a nine-dimensional task on MI355X.  With
+// this order and without events between the launches a run of 8 iterations of 20 000
+// second-order samples takes 182 us (270 before), one of 10 iterations of 2^18
+// fourth-order fp32 samples 357 us (439 before).
 __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int first_task,
                                                                    double alpha, int step_iter) {
   constexpr int NW = kFinishThreads / 64;
@@ -135,9 +174,32 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
   TaskDev *T = a.tasks + t;
   // the persistent launches of the next iteration claim items from zero
   if (a.queue && blockIdx.x == 0 && threadIdx.x < kQueueSlots) a.queue[threadIdx.x] = 0;
-  if (!T->active || T->plan <= step_iter) return;
+  // sample time of this iteration, kept by task 0: from the end of the last
+  // iteration's (or mark_start's) bookkeeping to here.  The device clock takes
+  // the place of a pair of events around every sample launch, which kept the
+  // launches 5-6 us apart on MI355X.
+  const bool clock = a.timed && t == 0;
+  const uint64_t now = clock ? wall_clock64() : 0;
+  if (!T->active || T->plan <= step_iter) {
+    if (clock && threadIdx.x == 0) {
+      T->t_busy += now - T->t_begin;
+      T->t_begin = wall_clock64();
+    }
+    return;
+  }
   const int tid = threadIdx.x, bs = blockDim.x;
+  const int wave = tid >> 6, lane = tid & 63;
   const int it0 = T->store_begin, it1 = T->store_begin + T->nitems;
+  const int nb = a.phys.nb, nd = T->nd;
+  const TaskState S0 = *T;  // as the iteration found it
+  const int train = T->train_iters;
+  // with a training phase the grid is frozen once the training iterations are
+  // done; dimension m belongs to wave (m + 1) mod NW
+  const bool refine = train <= 0 || S0.it_done < train;
+  double *hists = a.hists + T->hist_off, *grids = a.grids + T->grid_off;
+  const int m0 = (wave + NW - 1) % NW;
+  DimRegs dim{};
+  if (refine && m0 < nd) dim = load_dim(hists + m0 * nb, grids + m0 * (nb + 1), nb);
   // regularised components (same samples, main component's shift): item
   // sums in item order per thread, then across the block
   if (a.nreg > 0) {
@@ -154,9 +216,9 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
 #pragma unroll
       for (int j = 0; j < kRegSums; ++j) cs[j] += __shfl_xor(cs[j], off, 64);
     }
-    if ((tid & 63) == 0) {
+    if (lane == 0) {
 #pragma unroll
-      for (int j = 0; j < kRegSums; ++j) cred[tid >> 6][j] = cs[j];
+      for (int j = 0; j < kRegSums; ++j) cred[wave][j] = cs[j];
     }
   }
   double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0;
@@ -184,27 +246,29 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
       }
     }
   }
+  const int waves = min(NW, (it1 - it0 + 63) >> 6);  // waves that hold partials
+  if (wave < waves) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double os1 = __shfl_xor(s1, off, 64), oc1 = __shfl_xor(c1, off, 64);
-    const double os2 = __shfl_xor(s2, off, 64), oc2 = __shfl_xor(c2, off, 64);
-    pair_merge(s1, c1, os1, oc1);
-    pair_merge(s2, c2, os2, oc2);
-    for (int j = 0; j < kItemCounters; ++j) kc[j] += __shfl_xor(kc[j], off, 64);
-  }
-  const int wave = tid >> 6, lane = tid & 63;
-  if (lane == 0) {
-    red[4 * wave + 0] = s1;
-    red[4 * wave + 1] = c1;
-    red[4 * wave + 2] = s2;
-    red[4 * wave + 3] = c2;
-    for (int j = 0; j < kItemCounters; ++j) kred[wave][j] = kc[j];
+    for (int off = 32; off >= 1; off >>= 1) {
+      const double os1 = __shfl_xor(s1, off, 64), oc1 = __shfl_xor(c1, off, 64);
+      const double os2 = __shfl_xor(s2, off, 64), oc2 = __shfl_xor(c2, off, 64);
+      pair_merge(s1, c1, os1, oc1);
+      pair_merge(s2, c2, os2, oc2);
+      for (int j = 0; j < kItemCounters; ++j) kc[j] += __shfl_xor(kc[j], off, 64);
+    }
+    if (lane == 0) {
+      red[4 * wave + 0] = s1;
+      red[4 * wave + 1] = c1;
+      red[4 * wave + 2] = s2;
+      red[4 * wave + 3] = c2;
+      for (int j = 0; j < kItemCounters; ++j) kred[wave][j] = kc[j];
+    }
   }
   __syncthreads();
   if (tid == 0) {
     double S1 = red[0], C1 = red[1], S2 = red[2], C2 = red[3];
     unsigned long long F[kItemCounters] = {kred[0][0], kred[0][1], kred[0][2]};
-    for (int w = 1; w < (bs >> 6); ++w) {
+    for (int w = 1; w < waves; ++w) {
       pair_merge(S1, C1, red[4 * w + 0], red[4 * w + 1]);
       pair_merge(S2, C2, red[4 * w + 2], red[4 * w + 3]);
       for (int j = 0; j < kItemCounters; ++j) F[j] += kred[w][j];
@@ -214,9 +278,40 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
     const double m2 = (S2 + C2) / N;
     double var = (m2 - m1 * m1) / (N - 1.0);
     if (var < 0.0) var = 0.0;
-    const double I = T->shift + m1;
+    const double I = S0.shift + m1;
+    TaskState S = S0;
+    // training/evaluation split: the first evaluation iteration discards
+    // the training iterations from the running sums
+    if (train > 0 && S.it_done == train) {
+      S.wsum = S.wisum = S.wi2sum = S.zsum = 0.0;
+      S.nzero = 0;
+      S.ncomb = 0;
+    }
+    S.ncomb += 1;
+    if (var > 0.0) {
+      S.wsum += 1.0 / var;
+      S.wisum += I / var;
+      S.wi2sum += I * I / var;
+    } else {
+      S.nzero += 1;
+      S.zsum += I;
+    }
+    S.lastI = I;
+    S.lastV = var;
+    S.shift = I;
+    S.iter += 1;
+    S.it_done += 1;
+    S.nevals += T->nsamples;
+    S.nfallback += F[0];
+    S.npass += F[1];
+    S.nterms += F[2];
+    if (clock) {
+      S.t_busy += now - S.t_begin;
+      S.t_begin = wall_clock64();
+    }
+    *static_cast<TaskState *>(T) = S;
     if (T->res_cap > 0) {
-      const int slot = T->res_off + (T->it_done % T->res_cap);
+      const int slot = T->res_off + (S0.it_done % T->res_cap);
       double *lg = a.reslog + 2 * slot;
       lg[0] = I;
       lg[1] = var;
@@ -234,48 +329,21 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
           q2 /= N;
           double v = (q2 - q1 * q1) / (N - 1.0);
           if (v < 0.0) v = 0.0;
-          cl[2 * r] = T->shift + q1;
+          cl[2 * r] = S0.shift + q1;
           cl[2 * r + 1] = v;
         }
       }
     }
-    // training/evaluation split: the first evaluation iteration discards
-    // the training iterations from the running sums
-    if (T->train_iters > 0 && T->it_done == T->train_iters) {
-      T->wsum = T->wisum = T->wi2sum = T->zsum = 0.0;
-      T->nzero = 0;
-      T->ncomb = 0;
-    }
-    T->ncomb += 1;
-    if (var > 0.0) {
-      T->wsum += 1.0 / var;
-      T->wisum += I / var;
-      T->wi2sum += I * I / var;
-    } else {
-      T->nzero += 1;
-      T->zsum += I;
-    }
-    T->lastI = I;
-    T->lastV = var;
-    T->shift = I;
-    T->iter += 1;
-    T->it_done += 1;
-    T->nevals += T->nsamples;
-    T->nfallback += F[0];
-    T->npass += F[1];
-    T->nterms += F[2];
   }
-  // refinement: one wavefront per dimension; with a training phase the grid
-  // is frozen once the training iterations are done
-  __syncthreads();
-  const int nb = a.phys.nb;
-  const bool refine = T->train_iters <= 0 || T->it_done <= T->train_iters;
-  double *scr = scratch + static_cast<size_t>(wave) * (2 * nb + 2);
-  for (int m = wave; m < T->nd; m += (bs >> 6)) {
-    double *hist = a.hists + T->hist_off + m * nb;
-    double *edges = a.grids + T->grid_off + m * (nb + 1);
-    if (refine) refine_dim_wave(hist, edges, nb, alpha, scr);
-    __syncwarp();
+  // refinement, and the next iteration's zeroed histogram
+  double *scr = scratch + static_cast<size_t>(wave) * (3 * nb + 3);
+  for (int m = m0; m < nd; m += NW) {
+    double *hist = hists + m * nb, *edges = grids + m * (nb + 1);
+    if (refine) {
+      if (m != m0) dim = load_dim(hist, edges, nb);
+      refine_dim_wave(dim, edges, nb, alpha, scr);
+      __syncwarp();
+    }
     for (int b = lane; b < nb; b += 64) hist[b] = 0.0;
   }
 }
@@ -398,8 +466,12 @@ __global__ void init_tasks(KArgs a, int first, int keep_grid) {
     T->ncomb = 0;
     T->lastI = T->lastV = 0.0;
     T->nevals = T->nfallback = T->npass = T->nterms = 0;
+    T->t_begin = T->t_busy = 0;
   }
 }
+
+// Start of a timed launch sequence (see finish_iteration).
+__global__ void mark_start(TaskDev *tasks) { tasks[0].t_begin = wall_clock64(); }
 
 // ---------------------------------------------------------------------------
 // Host-side launchers
@@ -454,9 +526,14 @@ hipError_t launch_dump(const KArgs &a, int t, int order, int q, int prec, bool g
 hipError_t launch_finish(const KArgs &a, int first_task, int ntasks, int step_iter, double alpha,
                          hipStream_t st) {
   const size_t lds =
-      (kFinishThreads / 64) * static_cast<size_t>(2 * a.phys.nb + 2) * sizeof(double);
+      (kFinishThreads / 64) * static_cast<size_t>(3 * a.phys.nb + 3) * sizeof(double);
   hipLaunchKernelGGL(finish_iteration, dim3(ntasks), dim3(kFinishThreads), lds, st, a, first_task,
                      alpha, step_iter);
+  return hipGetLastError();
+}
+
+hipError_t launch_mark_start(const KArgs &a, hipStream_t st) {
+  hipLaunchKernelGGL(mark_start, dim3(1), dim3(1), 0, st, a.tasks);
   return hipGetLastError();
 }
 

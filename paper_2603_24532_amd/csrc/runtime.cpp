@@ -137,16 +137,15 @@ extern "C" int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context *
   ctx->v = mbpt_interaction{-1.0, -2.0, 0.7, 2.0, 4, 41.47, 197.3269804};
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, d.device) == hipSuccess) ctx->num_cus = prop.multiProcessorCount;
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, d.device) == hipSuccess && khz > 0)
+    ctx->clock_khz = khz;
   *out = ctx;
   return MBPT_OK;
 }
 
 extern "C" void mbpt_context_destroy(mbpt_context *ctx) {
   if (!ctx) return;
-  for (auto &ev : ctx->events) {
-    (void)hipEventDestroy(ev.first);
-    (void)hipEventDestroy(ev.second);
-  }
   delete ctx;
 }
 
@@ -821,7 +820,7 @@ int ensure_hf(mbpt_task_set *set) {
 // Upload the parameter prefix of every TaskDev (state left untouched).
 int upload_params(mbpt_task_set *set) {
   mbpt_context *ctx = set->ctx;
-  const size_t width = offsetof(TaskDev, iter);
+  const size_t width = sizeof(TaskParams);
   HIPCHK(ctx, hipMemcpy2DAsync(set->d_tasks, sizeof(TaskDev), set->h_tasks.data(), sizeof(TaskDev),
                                width, set->h_tasks.size(), hipMemcpyHostToDevice, ctx->stream));
   if (!set->olist.empty())
@@ -896,29 +895,11 @@ int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int 
   return MBPT_OK;
 }
 
-static hipEvent_t new_event() {
-  hipEvent_t e = nullptr;
-  (void)hipEventCreate(&e);
-  return e;
-}
-
-// Timing events around sample launches, resolved after the stream drains.
-void timed_begin(mbpt_context *ctx, size_t &slot) {
-  if (ctx->n_used == ctx->events.size()) ctx->events.emplace_back(new_event(), new_event());
-  slot = ctx->n_used++;
-  (void)hipEventRecord(ctx->events[slot].first, ctx->stream);
-}
-
-void timed_end(mbpt_context *ctx, size_t slot) { (void)hipEventRecord(ctx->events[slot].second, ctx->stream); }
-
-void resolve_timing(mbpt_context *ctx) {
-  for (size_t i = 0; i < ctx->n_used; ++i) {
-    float ms = 0.0f;
-    if (hipEventElapsedTime(&ms, ctx->events[i].first, ctx->events[i].second) == hipSuccess)
-      ctx->kernel_ms += ms;
-    ctx->launches += 1;
-  }
-  ctx->n_used = 0;
+// Sample-kernel time of a call from the device clock (see TaskState): `launches`
+// sample launches took `ticks`.
+void add_timing(mbpt_context *ctx, uint64_t launches, uint64_t ticks) {
+  ctx->launches += launches;
+  ctx->kernel_ms += static_cast<double>(ticks) / ctx->clock_khz;
 }
 
 void result_of(const TaskDev &S, mbpt_result &r) {
@@ -1192,7 +1173,9 @@ extern "C" int mbpt_reset(mbpt_task_set *set) {
 namespace mbpt {
 
 // Queue `iters` iterations of the whole set on the context stream.
-int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
+int enqueue_iterations(mbpt_task_set *set, KArgs a, int iters, bool timed) {
+  a.timed = timed;
+  if (timed) HIPCHK(set->ctx, launch_mark_start(a, set->ctx->stream));
   mbpt_context *ctx = set->ctx;
   const int nt = static_cast<int>(set->tasks.size());
   const double alpha = ctx->desc.alpha;
@@ -1201,12 +1184,9 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
     // tasks (independent of each other) share one launch
     for (int it = 0; it < iters; ++it) {
       for (int t = 0; t < nt; ++t) {
-        size_t slot = 0;
-        if (timed) timed_begin(ctx, slot);
         HIPCHK(ctx, launch_sample_order(a, set->tasks[t].order, set->q, ctx->desc.precision,
                                         set->task_ndiag[t] > 1, t, -1, set->h_tasks[t].nitems,
                                         set->block, ctx->stream));
-        if (timed) timed_end(ctx, slot);
       }
       HIPCHK(ctx, launch_finish(a, 0, nt, 0, alpha, ctx->stream));
     }
@@ -1215,8 +1195,6 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
   const bool persistent = set->launch_mode == MBPT_LAUNCH_PERSISTENT;
   const int prec = ctx->desc.precision;
   for (int it = 0; it < iters; ++it) {
-    size_t slot = 0;
-    if (timed) timed_begin(ctx, slot);
     for (const auto &r : set->oranges) {
       if (persistent) {
         HIPCHK(ctx, launch_sample_persistent(a, r.order, set->q, prec, r.group, r.k0, r.k1,
@@ -1226,7 +1204,6 @@ int enqueue_iterations(mbpt_task_set *set, KArgs &a, int iters, bool timed) {
                                         set->block, ctx->stream));
       }
     }
-    if (timed) timed_end(ctx, slot);
     HIPCHK(ctx, launch_finish(a, 0, nt, 0, alpha, ctx->stream));
   }
   return MBPT_OK;
@@ -1333,7 +1310,7 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
   }
   KArgs a = kargs_of(set);
   a.total_items = item;
-  uint64_t evals_before = 0;
+  uint64_t launches = 0;
   {
     int rc = 0;
     if (set->launch_mode == MBPT_LAUNCH_GRAPH && !set->noalloc) {
@@ -1345,7 +1322,7 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
         set->drop_graph();
         hipGraph_t graph = nullptr;
         HIPCHK(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
-        rc = enqueue_iterations(set, a, iters, false);
+        rc = enqueue_iterations(set, a, iters, true);
         hipError_t e = hipStreamEndCapture(ctx->stream, &graph);
         if (rc) return rc;
         if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamEndCapture");
@@ -1354,21 +1331,22 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
         if (e != hipSuccess) return hip_fail(ctx, e, "hipGraphInstantiate");
         set->graph_iters = iters;
       }
-      size_t slot = 0;
-      timed_begin(ctx, slot);
       HIPCHK(ctx, hipGraphLaunch(set->graph_exec, ctx->stream));
-      timed_end(ctx, slot);
+      launches = 1;
     } else {
       rc = enqueue_iterations(set, a, iters, !set->noalloc);
       if (rc) return rc;
+      if (!set->noalloc)
+        launches = static_cast<uint64_t>(iters) *
+                   (set->launch_mode == MBPT_LAUNCH_PER_TASK ? nt : 1);
     }
   }
-  (void)evals_before;
   std::vector<TaskDev> st(nt);
   HIPCHK(ctx, hipMemcpyAsync(st.data(), set->d_tasks, nt * sizeof(TaskDev), hipMemcpyDeviceToHost,
                              ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  resolve_timing(ctx);
+  add_timing(ctx, launches,
+             st[0].t_busy - (set->last_state.empty() ? 0 : set->last_state[0].t_busy));
   // FLOP accounting from the device counters of this call
   uint64_t evals = 0;
   double flops = 0.0;
@@ -1436,7 +1414,7 @@ namespace mbpt {
 // mbpt_integrate for a set without a workspace, inside device memory the
 // caller supplies for this call only: bind (uploads the descriptors and
 // parameters, starts every task from a uniform grid at iteration 0), run
-// without graph capture or timing events, then leave the set unbound.
+// without graph capture or timing, then leave the set unbound.
 int integrate_in(mbpt_task_set *set, void *base, size_t bytes, uint64_t samples_per_iter,
                  int iters, mbpt_result *per_task, mbpt_result *total) {
   if (!set || !base || iters < 1 || samples_per_iter < 2) return MBPT_EINVAL;

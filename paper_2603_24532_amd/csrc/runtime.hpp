@@ -36,8 +36,7 @@ struct mbpt_context {
   mbpt_interaction v{};
   int num_cus = 256;
   std::string err;
-  std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
-  size_t n_used = 0;
+  double clock_khz = 1e5;  // device clock of the sample-kernel times
   uint64_t launches = 0;
   double kernel_ms = 0.0;
   uint64_t evals = 0;
@@ -94,7 +93,7 @@ struct mbpt_task_set {
   std::vector<mbpt::OrderRange> oranges;   // one sample launch per order
   hipGraphExec_t graph_exec = nullptr;
   int graph_iters = 0;
-  // set while mbpt_integrate_noalloc runs: no graph capture, no timing events
+  // set while mbpt_integrate_noalloc runs: no graph capture, no timing
   bool noalloc = false;
   void drop_graph() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
@@ -129,9 +128,7 @@ bool fixed_masks_ok();
 Phys phys_of(const mbpt_context *ctx);  // all but the spectrum
 void fill_medium(const mbpt_context *ctx, double density, double x, TaskDev &T);
 void result_of(const TaskDev &S, mbpt_result &r);
-void timed_begin(mbpt_context *ctx, size_t &slot);
-void timed_end(mbpt_context *ctx, size_t slot);
-void resolve_timing(mbpt_context *ctx);
+void add_timing(mbpt_context *ctx, uint64_t launches, uint64_t ticks);
 void gauss_legendre(int n, double *x, double *w);
 int ensure_hf(mbpt_task_set *set);
 int sync_epoch(mbpt_task_set *set);

@@ -201,6 +201,7 @@ struct mbpt_server {
   int max_slots = 0, max_queue = 0;
   int spt = 16;  // samples per thread of the work items (server_spt)
   uint64_t max_samples = 0;
+  uint64_t busy_seen = 0;  // sample time of slot 0's record already counted
   char *ws = nullptr;
   Layout L{};
   Ranges items, bytes, diags;
@@ -413,6 +414,7 @@ int admit_one(mbpt_server *s, Req &q, int slot) {
   T.active = 1;
   s->h_tasks[slot] = T;
   *sT = T;
+  if (slot == 0) s->busy_seen = 0;
   char *b = s->ws;
   // asynchronous copies from pinned staging: the step's closing
   // synchronisation orders them before the staging is reused
@@ -672,7 +674,7 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     order_items(s->h_tasks, active, s->olist, s->ranges);
     std::memcpy(s->pin_tasks, s->h_tasks.data(), s->max_slots * sizeof(TaskDev));
     std::memcpy(s->pin_olist, s->olist.data(), s->olist.size() * sizeof(int2));
-    const size_t width = offsetof(TaskDev, iter);
+    const size_t width = sizeof(TaskParams);
     MBPT_HIPCHK(ctx, hipMemcpy2DAsync(s->ws + s->L.tasks, sizeof(TaskDev), s->pin_tasks,
                                       sizeof(TaskDev), width, s->max_slots, hipMemcpyHostToDevice,
                                       ctx->stream));
@@ -682,8 +684,8 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     KArgs a = server_kargs(s);
     a.total_items = s->ranges.back().item_end;
     const int prec = ctx->desc.precision;
-    size_t slot = 0;
-    timed_begin(ctx, slot);
+    a.timed = 1;
+    MBPT_HIPCHK(ctx, launch_mark_start(a, ctx->stream));
     for (int j = 0; j < K; ++j) {
       for (const auto &r : s->ranges) {
         int k1 = r.k0;  // end of the prefix still running in iteration j
@@ -695,7 +697,6 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
       }
       MBPT_HIPCHK(ctx, launch_finish(a, 0, s->max_slots, j, ctx->desc.alpha, ctx->stream));
     }
-    timed_end(ctx, slot);
     const TaskDev *st = s->pin_tasks;
     MBPT_HIPCHK(ctx, hipMemcpyAsync(s->pin_tasks, s->ws + s->L.tasks,
                                     s->max_slots * sizeof(TaskDev), hipMemcpyDeviceToHost,
@@ -707,7 +708,8 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
                                       hipMemcpyDeviceToHost, ctx->stream));
     MBPT_HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     s->stage_used = 0;
-    resolve_timing(ctx);
+    add_timing(ctx, 1, st[0].t_busy - s->busy_seen);
+    s->busy_seen = st[0].t_busy;
     const double t = now_s(s->t0);
     uint64_t evals = 0;
     double flops = 0.0;

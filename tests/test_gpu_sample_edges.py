@@ -58,3 +58,29 @@ def test_every_fourth_order_diagram(M, precision, mode, N, block, spt):
     and one launch for all, at proton fractions 0 to 0.8."""
     print(f"case all o4 {precision} mode={mode} N={N}", flush=True)
     _check_first_iteration(M, ALL4, N, precision, mode, block, spt)
+
+
+@pytest.mark.parametrize("order,did,nb,alpha", [
+    (2, 0, 2, 1.5), (2, 0, 3, 0.7), (2, 0, 63, 1.5), (2, 0, 64, 1.5), (2, 0, 65, 1.5),
+    (2, 0, 128, 0.7), (5, 42, 50, 1.5)])
+def test_refined_grid(M, order, did, nb, alpha):
+    """The grid after one iteration at the edges of the refinement's lanes (64
+    bins to a half) and waves (fifth order: 18 dimensions on 16 waves), at the
+    default compression exponent and another.  Histogram and edges are sums of
+    at most 10^4 rounded terms: 1e-10 absolute on edges in [0, 1]."""
+    N = 9001
+    print(f"case grid order={order} nb={nb} alpha={alpha}", flush=True)
+    ctx = M.mbpt_context_create(n_bins=nb, alpha=alpha)
+    try:
+        s = M.mbpt_create_task_set(ctx, [_task(order, did, 2, 0.12, 0.0, 5)])
+        nbytes = M.mbpt_workspace_query(s, N, 2)
+        buf, ptr = M.device_workspace(nbytes)
+        M.mbpt_bind_workspace(s, ptr, nbytes, N, 2)
+        M.mbpt_integrate(s, N, 1)
+        got = M.mbpt_get_grid(s, 0, 3 * (order + 1), nb)
+        M.mbpt_task_set_destroy(s)
+    finally:
+        M.mbpt_context_destroy(ctx)
+    pb = O.problem(order, did, density=0.12, seed=1, task_key=5, n_bins=nb, alpha=alpha)
+    _, _, _, edges = O.integrate(pb, N, 1)
+    assert np.abs(got - np.ravel(edges)).max() < 1e-10
