@@ -656,19 +656,35 @@ size_t items_for(const mbpt_task_set *set, uint64_t samples) {
   return static_cast<size_t>((samples + chunk - 1) / chunk);
 }
 
-// Samples per thread unless set explicitly, chosen at bind for the launch
-// mode the set has then: the larger of (a) a task's max_samples spread over
-// about two blocks per CU, at most 16 (one task's iteration lasts as long as
-// its slowest block), and (b) the samples of one launch spread over about 16
-// blocks per CU, at most 256 (a launch covers one task in the per-task mode,
-// all the tasks of an order otherwise): large work items halve the per-item
-// costs (grid and tables into LDS, the histogram merge, the last partial
-// fp64 re-evaluation round of the fp32 path) while a launch still spans many
-// rounds of blocks.
+// Samples per thread of the work items of a launch over `samples` samples.  An
+// item has fixed costs of about the time of ten samples per thread at one block
+// per CU (descriptor and grid into LDS, label tables, the last partly filled
+// fp64 re-evaluation round, the reduction, the histogram's atomics), so few
+// large items are better, but a launch lasts as long as its slowest CU.  With u
+// = samples per thread at one block per CU: up to four of them while that is at
+// least one block per CU, then 8, 16 and 32, which leaves two to sixteen blocks
+// per CU, and 16 blocks per CU from u = 512 on, so that the last round of blocks
+// is a small part.  Microseconds per iteration on MI355X, fourth order fp32 /
+// second order fp64, by samples per thread:
+//   u = 4:   1: 52 / 42, 2: 36 / 30, 4: 34 / 26, 8: 38 / 28
+//   u = 16:  4: 65 / 39, 8: 49 / 36, 16: 54 / 37, 32: 84 / 56
+//   u = 40:  4: 107 / 67, 8: 83 / 54, 16: 85 / 61, 32: 110 / 78
+//   u = 48:  4: 129 / 90, 8: 97 / 67, 16: 88 / 66, 32: 110 / 79
+//   u = 160: 8: 254 / 157, 16: 228 / 149, 32: 226 / 151, 64: 267 / 189
+int launch_spt(uint64_t samples, int block, int cus) {
+  const uint64_t u = samples / (static_cast<uint64_t>(block) * std::max(1, cus));
+  const uint64_t spt = u < 12    ? std::max<uint64_t>(1, std::min<uint64_t>(4, u))
+                       : u < 44  ? 8
+                       : u < 128 ? 16
+                       : u < 512 ? 32
+                                 : std::min<uint64_t>(256, u / 16);
+  return static_cast<int>(spt);
+}
+
+// Samples per thread unless set explicitly, chosen at bind for the launch mode
+// the set has then: a launch covers one task in the per-task mode, all the
+// tasks of an order otherwise.
 int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
-  const uint64_t cus = static_cast<uint64_t>(std::max(1, set->ctx->num_cus));
-  const uint64_t a =
-      std::max<uint64_t>(1, std::min<uint64_t>(16, max_samples / (set->block * 2 * cus)));
   uint64_t per_launch = max_samples;
   if (set->launch_mode != MBPT_LAUNCH_PER_TASK) {
     int count[kMaxOrder + 1] = {};
@@ -677,8 +693,7 @@ int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
       if (t.order >= 1 && t.order <= kMaxOrder) most = std::max(most, ++count[t.order]);
     per_launch = max_samples * static_cast<uint64_t>(most);
   }
-  const uint64_t b = std::min<uint64_t>(256, per_launch / (set->block * 16 * cus));
-  return static_cast<int>(std::max(a, b));
+  return launch_spt(per_launch, set->block, set->ctx->num_cus);
 }
 
 struct Layout {

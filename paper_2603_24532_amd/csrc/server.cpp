@@ -670,6 +670,19 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     return s->h_tasks[x].plan > s->h_tasks[y].plan;
   });
   const int nactive = static_cast<int>(active.size());
+  // samples per thread of each order's launches, from all the samples the first
+  // of them covers; never less than server_spt, which the requests' item
+  // memory is sized for
+  int spt_of[kMaxOrder + 1];
+  {
+    uint64_t samples[kMaxOrder + 1] = {};
+    for (int i : active) samples[s->h_tasks[i].order] += s->h_tasks[i].nsamples;
+    for (int o = 0; o <= kMaxOrder; ++o)
+      spt_of[o] = std::max(s->spt, launch_spt(samples[o], kBlock, ctx->num_cus));
+    for (int i : active)
+      s->h_tasks[i].nitems = static_cast<int>(
+          items_of(s->h_tasks[i].nsamples, spt_of[s->h_tasks[i].order]));
+  }
   if (nactive > 0) {
     order_items(s->h_tasks, active, s->olist, s->ranges);
     std::memcpy(s->pin_tasks, s->h_tasks.data(), s->max_slots * sizeof(TaskDev));
@@ -692,6 +705,7 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
         while (k1 < r.k1 && s->h_tasks[s->olist[k1].y].plan > j) ++k1;
         if (k1 == r.k0) continue;
         const int end = k1 < r.k1 ? s->olist[k1].x : r.item_end;
+        a.spt = spt_of[r.order];
         MBPT_HIPCHK(ctx, launch_sample_order(a, r.order, 4, prec, r.group, r.k0, k1,
                                              end - s->olist[r.k0].x, kBlock, ctx->stream));
       }
