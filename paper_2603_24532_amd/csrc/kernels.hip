@@ -194,7 +194,8 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
   const TaskState S0 = *T;  // as the iteration found it
   const int train = T->train_iters;
   // with a training phase the grid is frozen once the training iterations are
-  // done; dimension m belongs to wave (m + 1) mod NW
+  // done (the histogram is then zero, see adapts); dimension m belongs to wave
+  // (m + 1) mod NW
   const bool refine = train <= 0 || S0.it_done < train;
   double *hists = a.hists + T->hist_off, *grids = a.grids + T->grid_off;
   const int m0 = (wave + NW - 1) % NW;
@@ -337,13 +338,11 @@ __global__ __launch_bounds__(kFinishThreads) void finish_iteration(KArgs a, int 
   }
   // refinement, and the next iteration's zeroed histogram
   double *scr = scratch + static_cast<size_t>(wave) * (3 * nb + 3);
-  for (int m = m0; m < nd; m += NW) {
+  for (int m = m0; refine && m < nd; m += NW) {
     double *hist = hists + m * nb, *edges = grids + m * (nb + 1);
-    if (refine) {
-      if (m != m0) dim = load_dim(hist, edges, nb);
-      refine_dim_wave(dim, edges, nb, alpha, scr);
-      __syncwarp();
-    }
+    if (m != m0) dim = load_dim(hist, edges, nb);
+    refine_dim_wave(dim, edges, nb, alpha, scr);
+    __syncwarp();
     for (int b = lane; b < nb; b += 64) hist[b] = 0.0;
   }
 }
