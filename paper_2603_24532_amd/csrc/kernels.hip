@@ -475,13 +475,12 @@ __global__ void mark_start(TaskDev *tasks) { tasks[0].t_begin = wall_clock64(); 
 // ---------------------------------------------------------------------------
 // Host-side launchers
 
-size_t sample_lds_bytes(int nd, int nb, int block, int ntab) {
+size_t sample_lds_bytes(int nd, int nb, int block, int ntab, int wave_words) {
   // turn and 2^(j/64) tables + HF tables + grid pairs + histogram + reduction
-  // scratch + fp64 re-evaluation and Pauli screen queues (128 sample offsets
-  // per wavefront each)
+  // scratch + the wavefronts' queues + alignment of the label tables
   return fixed_lds_bytes() + hf_lds_doubles(ntab) * sizeof(double) +
          (3 * static_cast<size_t>(nd) * nb + 6 * (block / 64)) * sizeof(double) +
-         (block / 64) * 256 * sizeof(uint32_t) + 16;  // + alignment of the label tables
+         (block / 64) * wave_words * sizeof(uint32_t) + 16;
 }
 
 // Dispatch on (order, q) to the launchers of kernels_inst.hip.

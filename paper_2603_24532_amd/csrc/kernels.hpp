@@ -6,8 +6,9 @@
 
 namespace mbpt {
 
-// Dynamic LDS of a sample kernel; ntab = HF spline tables held (0, 1 or 2).
-size_t sample_lds_bytes(int nd, int nb, int block, int ntab);
+// Dynamic LDS of a sample kernel without its label tables; ntab = HF spline
+// tables held (0, 1 or 2), wave_words = queue words per wavefront.
+size_t sample_lds_bytes(int nd, int nb, int block, int ntab, int wave_words);
 // Items [olist[k0].x, olist[k0].x + nitems) of the tasks listed in olist[k0, k1),
 // or with k1 < 0 the nitems items of task k0.
 // group: tasks of several descriptors may be present (diagram groups).

@@ -237,34 +237,24 @@ __host__ __device__ constexpr size_t hf_lds_doubles(int ntab) {
   return static_cast<size_t>(ntab) * kHfEntries * 4;
 }
 
-// Carves the block's dynamic LDS; returns the first free double after the
-// grid pairs and fills the pointers.  Copies the turn and HF tables (the grid
-// pairs are the caller's).
-__device__ __forceinline__ double *carve_lds(const KArgs &a, const TaskDev *__restrict__ T,
-                                             int ntab, int nd, double *smem, SampleLds &L,
-                                             double2 *&g) {
-  SinCos *turn = reinterpret_cast<SinCos *>(smem);
-  double *ex = reinterpret_cast<double *>(turn + kTurnEntries);
-  double *hf = ex + kExp2Entries;
-  g = reinterpret_cast<double2 *>(hf + hf_lds_doubles(ntab));
-  load_turn_table(turn, ex);
-  if (ntab) {
-    const double *src = a.hf + 4 * static_cast<size_t>(T->hf_off);
-    const int n = static_cast<int>(hf_lds_doubles(ntab));
-    for (int i = threadIdx.x; i < n; i += blockDim.x) hf[i] = src[i];
+// HF splines in LDS: the (a, b) coefficients of every entry of the ntab tables,
+// then the (c, d): a gather of 16-byte pairs spreads over all the banks, where
+// pairs of a 32-byte entry fall on half of them.
+template <int NTAB>
+__device__ __forceinline__ void load_hf(double *hf, const double *__restrict__ src) {
+  constexpr int n = NTAB * kHfEntries;
+  double2 *ab = reinterpret_cast<double2 *>(hf), *cd = ab + n;
+  const double2 *e = reinterpret_cast<const double2 *>(src);
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    ab[i] = e[2 * i];
+    cd[i] = e[2 * i + 1];
   }
-  L.turn = turn;
-  L.ex = ex;
-  L.hf = ntab ? hf : nullptr;
-  L.g = g;
-  L.cyc = nullptr;
-  return reinterpret_cast<double *>(g + nd * a.phys.nb);
 }
-
-// HF self-energy of table tau at |k| = kk from the LDS spline (constant
-// beyond the last node).
-__device__ __forceinline__ double hf_sigma(const double *__restrict__ hf, int tau, double kk,
-                                           double inv_h) {
+// HF self-energies of the NTAB isospin tables at |k| = kk from the LDS splines
+// (constant beyond the last node).
+template <int NTAB>
+__device__ __forceinline__ void hf_sigma(const double *__restrict__ hf, double kk, double inv_h,
+                                         double *sigma) {
   const double u = kk * inv_h;
   int i = static_cast<int>(u);
   double t = u - static_cast<double>(i);
@@ -272,8 +262,33 @@ __device__ __forceinline__ double hf_sigma(const double *__restrict__ hf, int ta
     i = kHfIntervals;
     t = 0.0;
   }
-  const double *e = hf + 4 * (tau * kHfEntries + i);
-  return fma(t, fma(t, fma(t, e[3], e[2]), e[1]), e[0]);
+  const double2 *ab = reinterpret_cast<const double2 *>(hf), *cd = ab + NTAB * kHfEntries;
+#pragma unroll
+  for (int tau = 0; tau < NTAB; ++tau) {
+    const double2 p = ab[tau * kHfEntries + i], q = cd[tau * kHfEntries + i];
+    sigma[tau] = fma(t, fma(t, fma(t, q.y, q.x), p.y), p.x);
+  }
+}
+
+// Carves the block's dynamic LDS; returns the first free double after the
+// grid pairs and fills the pointers.  Copies the turn and HF tables (the grid
+// pairs are the caller's).
+template <int ntab>
+__device__ __forceinline__ double *carve_lds(const KArgs &a, const TaskDev *__restrict__ T,
+                                             int nd, double *smem, SampleLds &L,
+                                             double2 *&g) {
+  SinCos *turn = reinterpret_cast<SinCos *>(smem);
+  double *ex = reinterpret_cast<double *>(turn + kTurnEntries);
+  double *hf = ex + kExp2Entries;
+  g = reinterpret_cast<double2 *>(hf + hf_lds_doubles(ntab));
+  load_turn_table(turn, ex);
+  if constexpr (ntab > 0) load_hf<ntab>(hf, a.hf + 4 * static_cast<size_t>(T->hf_off));
+  L.turn = turn;
+  L.ex = ex;
+  L.hf = ntab ? hf : nullptr;
+  L.g = g;
+  L.cyc = nullptr;
+  return reinterpret_cast<double *>(g + nd * a.phys.nb);
 }
 
 // sin and cos of 2 pi u / 128 for u in [0, 128]: the nearest table angle
@@ -1125,8 +1140,7 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
   constexpr int NL = 2 * ORDER;
   constexpr int NC = ORDER - 1;
 
-  // line momenta -> occupation tests and energies (HF: plus the self-energy
-  // of a neutron, and for nuclear matter the proton-neutron difference)
+  // line momenta -> occupation tests and energies
   double eps[NL], deps[NL];
   uint32_t inN = 0, inP = 0;  // bit l: line l inside the Fermi sphere
 #pragma unroll
@@ -1147,13 +1161,6 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     // the free spectrum's energies in units of hbar^2 / 2m (energy_unit)
     eps[l] = k2;
     deps[l] = 0.0;
-    if constexpr (HF) {
-      eps[l] = a.phys.hb2m * k2;
-      const double kk = sqrt_normal(k2);
-      const double sn = hf_sigma(Ls.hf, 0, kk, T->hf_inv_h);
-      if (Q == 4) deps[l] = hf_sigma(Ls.hf, 1, kk, T->hf_inv_h) - sn;
-      eps[l] += sn;
-    }
     inN = push_sign(inN, k2 - T->kF2[0]);
     if (Q == 4) inP = push_sign(inP, k2 - T->kF2[1]);
   }
@@ -1165,6 +1172,19 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
   if (!label_state<ORDER, Q, V, LF>(a, D, Ls, okN, okP, ls)) return 0.0;
   if constexpr (SCR) return 1.0;  // the Pauli screen (see screen_on)
   ++npass;
+
+  // HF: the energies in MeV plus the self-energy of a neutron, and for nuclear
+  // matter the proton-neutron difference, of the samples that pass only (the
+  // spline gathers are what the kernel waits for)
+  if constexpr (HF) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      double sigma[Q == 4 ? 2 : 1];
+      hf_sigma<(Q == 4 ? 2 : 1)>(Ls.hf, sqrt_normal(eps[l]), T->hf_inv_h, sigma);
+      eps[l] = fma(a.phys.hb2m, eps[l], sigma[0]);
+      if constexpr (Q == 4) deps[l] = sigma[1] - sigma[0];
+    }
+  }
 
   // energy denominators (with every line a neutron when they depend on
   // isospin; the label sum then corrects them per configuration)
@@ -1539,6 +1559,15 @@ constexpr bool screen_on() {
   return ORDER >= 5 && (P == 0 || P == 1) && !X;
 }
 
+// Words of a wavefront's LDS: the fp64 re-evaluation queue (fp32 kernels) and the
+// Pauli screen's, 128 sample offsets each; the component sums of the regularised
+// kernels, which have neither.
+template <int ORDER, int Q, int P, bool X>
+constexpr int wave_words() {
+  return (prec_of<P>() == 1 ? 128 : 0) + (screen_on<ORDER, Q, P, X>() ? 128 : 0) +
+         (reg_of<P>() ? 2 * kRegSums : 0);
+}
+
 // Appends the lanes with `flag` set to a wavefront's queue in LDS (ballot
 // order, so the order is deterministic); n is wave-uniform.
 __device__ __forceinline__ void wave_queue_push(uint32_t *q, int &n, bool flag, uint32_t v) {
@@ -1600,8 +1629,7 @@ constexpr int lds_tables() {
 // regulator exponent's half fixed at compile time, or 0, see reg_pow)
 
 // LDS of a sample block: turn and 2^(j/64) tables, HF tables, grid (e, width)
-// pairs, histogram, reduction scratch, fp64 re-evaluation queues and Pauli
-// screen queues (128 sample offsets per wavefront each), label
+// pairs, histogram, reduction scratch, the wavefronts' queues (wave_words), label
 // table(s).
 struct BlockLds {
   SampleLds Ls;
@@ -1627,7 +1655,7 @@ __device__ __forceinline__ void block_lds(const KArgs &a, double *smem, BlockLds
   B.Ls.hf = ntab ? hf : nullptr;
   B.Ls.g = B.g;
   size_t end = reinterpret_cast<char *>(B.red + 6 * nw) - reinterpret_cast<char *>(smem);
-  end = (end + 256 * nw * sizeof(uint32_t) + 15) & ~size_t{15};
+  end = (end + wave_words<ORDER, Q, P, X>() * nw * sizeof(uint32_t) + 15) & ~size_t{15};
   B.Ls.cyc = reinterpret_cast<char *>(smem) + end;
   load_turn_table(turn, ex);
 }
@@ -1642,12 +1670,8 @@ __device__ __forceinline__ void task_lds(const KArgs &a, int t, BlockLds &B) {
   const TaskDev *__restrict__ T = a.tasks + t;
   const int nb = a.phys.nb;
   const int tid = threadIdx.x, bs = blockDim.x;
-  if constexpr (ntab > 0) {
-    double *hf = const_cast<double *>(B.Ls.hf);
-    const double *src = a.hf + 4 * static_cast<size_t>(T->hf_off);
-    const int n = static_cast<int>(hf_lds_doubles(ntab));
-    for (int i = tid; i < n; i += bs) hf[i] = src[i];
-  }
+  if constexpr (ntab > 0)
+    load_hf<ntab>(const_cast<double *>(B.Ls.hf), a.hf + 4 * static_cast<size_t>(T->hf_off));
   const double *ge = a.grids + T->grid_off;
   const DiagDev *__restrict__ D = a.diags + T->diag;
   for (int i = tid; i < ND * nb; i += bs) {
@@ -1734,8 +1758,9 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
   constexpr bool SCR = screen_on<ORDER, Q, P, X>();
   const int lane = tid & 63;
   // per wavefront: the fp64 re-evaluation queue, then the Pauli screen's
-  uint32_t *queue = reinterpret_cast<uint32_t *>(red + 6 * (bs >> 6)) + 128 * (tid >> 6);
-  uint32_t *pqueue = queue + 128 * (bs >> 6);
+  uint32_t *queue = reinterpret_cast<uint32_t *>(red + 6 * (bs >> 6)) +
+                    wave_words<ORDER, Q, P, X>() * (tid >> 6);
+  uint32_t *pqueue = queue + (PP == 1 ? 128 : 0);
   // the sample loops, specialised per diagram variant (uniform per item)
   auto loops = [&](auto vt) {
     constexpr int V = decltype(vt)::value;
@@ -1893,7 +1918,6 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
   }
   const int wave = tid >> 6;
   uint32_t *ured = reinterpret_cast<uint32_t *>(red + 4 * (bs >> 6));
-  // component sums per wave in the (fp64-only, so unused) re-evaluation queue
   double *rred = red + 6 * (bs >> 6);
   if constexpr (R) {
     if (lane == 0) {
@@ -2106,7 +2130,7 @@ __global__ __launch_bounds__(256) void dump_samples(KArgs a, int t, uint32_t ite
   const int nb = a.phys.nb;
   SampleLds Ls;
   double2 *g;
-  carve_lds(a, T, lds_tables<Q, P>(), ND, smem, Ls, g);
+  carve_lds<lds_tables<Q, P>()>(a, T, ND, smem, Ls, g);
   const double *ge = a.grids + T->grid_off;
   for (int i = threadIdx.x; i < ND * nb; i += blockDim.x) {
     const int m = i / nb, b = i - m * nb;

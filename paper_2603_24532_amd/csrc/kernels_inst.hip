@@ -57,7 +57,8 @@ hipError_t launch_order_oq<O, Q>(const KArgs &a, int prec, bool group, int k0, i
     if constexpr (fixed4<O, Q, P, X, HE>()) {
       return launch_o4_fixed<P>(a, k0, k1, grid, block, st);
     } else {
-      const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
+      const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>(),
+                                        wave_words<O, Q, P, X>()) +
                          label_lds_bytes<O, Q, P, X>();
       hipLaunchKernelGGL((sample_order<O, Q, P, X, HE>), dim3(grid), dim3(block), lds, st, a, k0,
                          k1);
@@ -74,7 +75,8 @@ hipError_t launch_persist_oq<O, Q>(const KArgs &a, int prec, bool group, int k0,
     constexpr int P = decltype(p)::value;
     constexpr bool X = decltype(x)::value;
     constexpr int HE = decltype(h)::value;
-    const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
+    const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>(),
+                                        wave_words<O, Q, P, X>()) +
                        label_lds_bytes<O, Q, P, X>();
     auto kern = sample_persistent<O, Q, P, X, HE>;
     // more blocks than can be resident: the extra ones start as others

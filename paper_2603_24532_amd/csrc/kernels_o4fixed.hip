@@ -14,7 +14,8 @@ template <>
 hipError_t launch_o4_fixed<MBPT_FIXED_P>(const KArgs &a, int k0, int k1, int grid, int block,
                                          hipStream_t st) {
   constexpr int O = 4, Q = 4, P = MBPT_FIXED_P;
-  const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>()) +
+  const size_t lds = sample_lds_bytes(3 * (O + 1), a.phys.nb, block, lds_tables<Q, P>(),
+                                        wave_words<O, Q, P, false>()) +
                      label_lds_bytes<O, Q, P, false>();
   hipLaunchKernelGGL((sample_order<O, Q, P, false, 2>), dim3(grid), dim3(block), lds, st, a, k0,
                      k1);
