@@ -272,6 +272,14 @@ constexpr int kPersistentBlocksPerCu = 16;
 // terms evaluated.
 constexpr int kItemCounters = 3;
 
+// One piece of a copy launch (see copy_pieces): up to kCopyWords 4-byte words.
+constexpr int kCopyWords = 1024;
+struct CopySeg {
+  void *dst;
+  const void *src;
+  uint64_t words;
+};
+
 struct KArgs {
   TaskDev *tasks;
   const DiagDev *diags;

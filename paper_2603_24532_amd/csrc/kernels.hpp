@@ -25,6 +25,7 @@ hipError_t launch_finish(const KArgs &a, int first_task, int ntasks, int step_it
                          hipStream_t st);
 // Stamps the start of a timed launch sequence (KArgs::timed) in task 0's state.
 hipError_t launch_mark_start(const KArgs &a, hipStream_t st);
+hipError_t launch_copy(const CopySeg *segs, int n, hipStream_t st);
 // out_reg (regularised components, count * nreg; may be null) is written only
 // when a.nreg > 0.
 hipError_t launch_dump(const KArgs &a, int task, int order, int q, int prec, bool group,

@@ -1228,7 +1228,7 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
   if constexpr (REG) {
     // num / den / x for x = prod_c D_c and the shifted products of the
     // components, with one reciprocal: one per component and one for the rest
-    // took 4 % of a pass over the grouped fourth-order diagrams (four
+    // took 4 % of a pass over the grouped fourth-order diagrams (three
     // components, 2^18 samples: 12.36 -> 11.88 ms). The numerator, tiny far out, enters last: the
     // products alone stay far from the ends of the exponent.
     double x[kMaxReg], pre[kMaxReg];

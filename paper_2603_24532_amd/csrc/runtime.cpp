@@ -140,12 +140,20 @@ extern "C" int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context *
   int khz = 0;
   if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, d.device) == hipSuccess && khz > 0)
     ctx->clock_khz = khz;
+  if (hipHostMalloc(reinterpret_cast<void **>(&ctx->pin), kPinBytes + kPinSegs * sizeof(CopySeg),
+                    hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->pin = nullptr;
+  }
   *out = ctx;
   return MBPT_OK;
 }
 
 extern "C" void mbpt_context_destroy(mbpt_context *ctx) {
   if (!ctx) return;
+  // (a copy may still be queued; the caller's stream may be gone already)
+  if (ctx->pin && (ctx->pin_used || ctx->pin_segs_used)) (void)hipDeviceSynchronize();
+  if (ctx->pin) (void)hipHostFree(ctx->pin);
   delete ctx;
 }
 
@@ -832,16 +840,101 @@ int ensure_hf(mbpt_task_set *set) {
   return MBPT_OK;
 }
 
+static_assert(sizeof(TaskParams) % 4 == 0 && sizeof(TaskDev) % 4 == 0 &&
+                  sizeof(DiagDev) % 4 == 0 && sizeof(GroupDev) % 4 == 0 &&
+                  sizeof(TermDev) % 4 == 0,
+              "copied in 4-byte words");
+
+// Queued pieces are cut to what one block of the copy kernel moves.
+void queue_copy(mbpt_context *ctx, void *dst, const void *src, size_t bytes) {
+  for (size_t at = 0; at < bytes; at += 4 * kCopyWords)
+    ctx->segs.push_back({static_cast<char *>(dst) + at, static_cast<const char *>(src) + at,
+                         std::min<size_t>(bytes - at, 4 * kCopyWords) / 4});
+}
+
+int flush_copies(mbpt_context *ctx) {
+  std::vector<CopySeg> segs;
+  segs.swap(ctx->segs);
+  if (!ctx->pin) {
+    for (const CopySeg &g : segs)
+      HIPCHK(ctx, hipMemcpyAsync(g.dst, g.src, 4 * g.words, hipMemcpyDefault, ctx->stream));
+    return MBPT_OK;
+  }
+  for (size_t at = 0, n; at < segs.size(); at += n) {
+    n = std::min(segs.size() - at, kPinSegs);
+    if (ctx->pin_segs_used + n > kPinSegs) {
+      HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+      ctx->pin_segs_used = 0;
+    }
+    CopySeg *list = reinterpret_cast<CopySeg *>(ctx->pin + kPinBytes) + ctx->pin_segs_used;
+    ctx->pin_segs_used += n;
+    std::memcpy(list, segs.data() + at, n * sizeof(CopySeg));
+    HIPCHK(ctx, launch_copy(list, static_cast<int>(n), ctx->stream));
+  }
+  return MBPT_OK;
+}
+
+int queue_upload(mbpt_context *ctx, void *dst, const void *src, size_t bytes) {
+  if (!bytes) return MBPT_OK;
+  const size_t need = (bytes + 63) & ~size_t{63};
+  if (!ctx->pin || need > kPinBytes) {
+    const int rc = flush_copies(ctx);
+    if (rc) return rc;
+    HIPCHK(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, ctx->stream));
+    return MBPT_OK;
+  }
+  if (ctx->pin_used + need > kPinBytes) {  // full: what is queued first
+    const int rc = flush_copies(ctx);
+    if (rc) return rc;
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    stream_done(ctx);
+  }
+  std::memcpy(ctx->pin + ctx->pin_used, src, bytes);
+  queue_copy(ctx, dst, ctx->pin + ctx->pin_used, bytes);
+  ctx->pin_used += need;
+  return MBPT_OK;
+}
+
+int read_back(mbpt_context *ctx, const HostCopy *c, int n) {
+  size_t total = 0;
+  for (int i = 0; i < n; ++i) total += (c[i].bytes + 63) & ~size_t{63};
+  const bool staged = ctx->pin && ctx->pin_used + total <= kPinBytes;
+  const char *p = ctx->pin + ctx->pin_used;
+  for (int i = 0; i < n; ++i) {
+    if (staged) {
+      queue_copy(ctx, ctx->pin + ctx->pin_used, c[i].src, c[i].bytes);
+      ctx->pin_used += (c[i].bytes + 63) & ~size_t{63};
+    } else {
+      HIPCHK(ctx, hipMemcpyAsync(c[i].dst, c[i].src, c[i].bytes, hipMemcpyDeviceToHost,
+                                 ctx->stream));
+    }
+  }
+  const int rc = flush_copies(ctx);
+  if (rc) return rc;
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  if (staged)
+    for (int i = 0; i < n; p += (c[i].bytes + 63) & ~size_t{63}, ++i)
+      std::memcpy(c[i].dst, p, c[i].bytes);
+  stream_done(ctx);
+  return MBPT_OK;
+}
+
 // Upload the parameter prefix of every TaskDev (state left untouched).
 int upload_params(mbpt_task_set *set) {
   mbpt_context *ctx = set->ctx;
-  const size_t width = sizeof(TaskParams);
-  HIPCHK(ctx, hipMemcpy2DAsync(set->d_tasks, sizeof(TaskDev), set->h_tasks.data(), sizeof(TaskDev),
-                               width, set->h_tasks.size(), hipMemcpyHostToDevice, ctx->stream));
-  if (!set->olist.empty())
-    HIPCHK(ctx, hipMemcpyAsync(set->d_olist, set->olist.data(), set->olist.size() * sizeof(int2),
-                               hipMemcpyHostToDevice, ctx->stream));
-  return MBPT_OK;
+  const size_t nt = set->h_tasks.size();
+  int rc = MBPT_OK;
+  if (ctx->pin && nt * (sizeof(TaskParams) + 64) <= kPinBytes) {
+    for (size_t t = 0; t < nt && !rc; ++t)
+      rc = queue_upload(ctx, set->d_tasks + t, &set->h_tasks[t], sizeof(TaskParams));
+  } else {
+    HIPCHK(ctx, hipMemcpy2DAsync(set->d_tasks, sizeof(TaskDev), set->h_tasks.data(),
+                                 sizeof(TaskDev), sizeof(TaskParams), nt, hipMemcpyHostToDevice,
+                                 ctx->stream));
+  }
+  if (!rc)
+    rc = queue_upload(ctx, set->d_olist, set->olist.data(), set->olist.size() * sizeof(int2));
+  return rc ? rc : flush_copies(ctx);
 }
 
 int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int max_iters) {
@@ -883,28 +976,25 @@ int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int 
   set->run_reg_n = -1;
   set->h_gl.assign(2 * kHfGauss, 0.0);
   gauss_legendre(kHfGauss, set->h_gl.data(), set->h_gl.data() + kHfGauss);
-  HIPCHK(ctx, hipMemcpyAsync(set->d_gl, set->h_gl.data(), set->h_gl.size() * sizeof(double),
-                             hipMemcpyHostToDevice, ctx->stream));
   set->hf_dirty = true;
   fill_task_params(set);
   set->oranges.clear();
-  HIPCHK(ctx, hipMemcpyAsync(set->d_diags, set->diags.data(), set->diags.size() * sizeof(DiagDev),
-                             hipMemcpyHostToDevice, ctx->stream));
-  if (!set->groups.empty())
-    HIPCHK(ctx, hipMemcpyAsync(set->d_groups, set->groups.data(),
-                               set->groups.size() * sizeof(GroupDev), hipMemcpyHostToDevice,
-                               ctx->stream));
-  if (!set->terms.empty())
-    HIPCHK(ctx, hipMemcpyAsync(set->d_terms, set->terms.data(), set->terms.size() * sizeof(TermDev),
-                               hipMemcpyHostToDevice, ctx->stream));
-  if (!set->coefs.empty())
-    HIPCHK(ctx, hipMemcpyAsync(set->d_coefs, set->coefs.data(), set->coefs.size() * sizeof(double),
-                               hipMemcpyHostToDevice, ctx->stream));
-  int rc = upload_params(set);
+  int rc = queue_upload(ctx, set->d_gl, set->h_gl.data(), set->h_gl.size() * sizeof(double));
+  if (!rc)
+    rc = queue_upload(ctx, set->d_diags, set->diags.data(), set->diags.size() * sizeof(DiagDev));
+  if (!rc)
+    rc = queue_upload(ctx, set->d_groups, set->groups.data(),
+                      set->groups.size() * sizeof(GroupDev));
+  if (!rc)
+    rc = queue_upload(ctx, set->d_terms, set->terms.data(), set->terms.size() * sizeof(TermDev));
+  if (!rc)
+    rc = queue_upload(ctx, set->d_coefs, set->coefs.data(), set->coefs.size() * sizeof(double));
+  if (!rc) rc = upload_params(set);
   if (rc) return rc;
   KArgs a = kargs_of(set);
   HIPCHK(ctx, launch_init(a, 0, static_cast<int>(set->tasks.size()), ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  stream_done(ctx);
   set->drop_graph();
   set->last_state.clear();
   return MBPT_OK;
@@ -1096,6 +1186,7 @@ static int move_eos_point(mbpt_task_set *set) {
   KArgs a = kargs_of(set);
   HIPCHK(ctx, launch_init(a, 0, static_cast<int>(set->tasks.size()), ctx->stream, true));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  stream_done(ctx);
   set->last_state.clear();
   set->run_reg_n = -1;
   return MBPT_OK;
@@ -1180,6 +1271,7 @@ extern "C" int mbpt_reset(mbpt_task_set *set) {
   KArgs a = kargs_of(set);
   HIPCHK(ctx, launch_init(a, 0, static_cast<int>(set->tasks.size()), ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  stream_done(ctx);
   set->last_state.clear();
   set->run_reg_n = -1;
   return MBPT_OK;
@@ -1357,9 +1449,11 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
     }
   }
   std::vector<TaskDev> st(nt);
-  HIPCHK(ctx, hipMemcpyAsync(st.data(), set->d_tasks, nt * sizeof(TaskDev), hipMemcpyDeviceToHost,
-                             ctx->stream));
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  {
+    const HostCopy state{st.data(), set->d_tasks, nt * sizeof(TaskDev)};
+    const int rc = read_back(ctx, &state, 1);
+    if (rc) return rc;
+  }
   add_timing(ctx, launches,
              st[0].t_busy - (set->last_state.empty() ? 0 : set->last_state[0].t_busy));
   // FLOP accounting from the device counters of this call
@@ -1485,12 +1579,13 @@ extern "C" int mbpt_iteration_log(mbpt_task_set *set, int task, double *I, doubl
   if (!set->ws) return MBPT_ESTATE;
   mbpt_context *ctx = set->ctx;
   TaskDev S;
-  HIPCHK(ctx, hipMemcpyAsync(&S, set->d_tasks + task, sizeof(TaskDev), hipMemcpyDeviceToHost,
-                             ctx->stream));
   std::vector<double> lg(2 * set->max_iters);
-  HIPCHK(ctx, hipMemcpyAsync(lg.data(), set->d_reslog + 2 * static_cast<size_t>(task) * set->max_iters,
-                             lg.size() * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  const HostCopy pieces[2] = {
+      {&S, set->d_tasks + task, sizeof(TaskDev)},
+      {lg.data(), set->d_reslog + 2 * static_cast<size_t>(task) * set->max_iters,
+       lg.size() * sizeof(double)}};
+  const int rc = read_back(ctx, pieces, 2);
+  if (rc) return rc;
   const int n = std::min(std::min(S.it_done, set->max_iters), cap);
   const int start = S.it_done - n;  // oldest stored iteration that fits
   for (int k = 0; k < n; ++k) {
@@ -1570,13 +1665,13 @@ extern "C" int mbpt_regularized_log(mbpt_task_set *set, int task, double *I, dou
   mbpt_context *ctx = set->ctx;
   const int K = set->run_reg_n > 0 ? set->run_reg_n : 0;
   TaskDev S;
-  HIPCHK(ctx, hipMemcpyAsync(&S, set->d_tasks + task, sizeof(TaskDev), hipMemcpyDeviceToHost,
-                             ctx->stream));
   const size_t per = kRegSums;
   std::vector<double> lg(per * set->max_iters);
-  HIPCHK(ctx, hipMemcpyAsync(lg.data(), set->d_creslog + per * task * set->max_iters,
-                             lg.size() * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  const HostCopy pieces[2] = {{&S, set->d_tasks + task, sizeof(TaskDev)},
+                              {lg.data(), set->d_creslog + per * task * set->max_iters,
+                               lg.size() * sizeof(double)}};
+  const int rc = read_back(ctx, pieces, 2);
+  if (rc) return rc;
   const int n = K > 0 ? std::min(std::min(S.it_done, set->max_iters), cap) : 0;
   const int start = S.it_done - n;
   // columns: components 1..K, then the extrapolation (last pair of a log entry)

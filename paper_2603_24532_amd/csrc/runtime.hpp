@@ -45,6 +45,12 @@ struct mbpt_context {
   int reg_n = 0;         // regularised components (0: none)
   double reg_eta = 0.0;  // component k shifts every denominator by -k reg_eta
   double fp32_rel_target = 0.0;  // see mbpt_set_fp32_target
+  // pinned staging: kPinBytes of data and a list of kPinSegs pieces (null: none
+  // could be had, ordinary copies are used instead), the fill of both since the
+  // stream was last waited for, and the pieces queued for the next copy launch
+  char *pin = nullptr;
+  size_t pin_used = 0, pin_segs_used = 0;
+  std::vector<mbpt::CopySeg> segs;
 };
 
 struct mbpt_task_set {
@@ -130,6 +136,27 @@ Phys phys_of(const mbpt_context *ctx);  // all but the spectrum
 void fill_medium(const mbpt_context *ctx, double density, double x, TaskDev &T);
 void result_of(const TaskDev &S, mbpt_result &r);
 void add_timing(mbpt_context *ctx, uint64_t launches, uint64_t ticks);
+
+// Staged copies. Transfers of up to kPinBytes go through the context's pinned
+// memory and one launch of copy_pieces; larger ones, where the copy engine is
+// the faster, are ordinary copies. Byte counts are multiples of four.
+constexpr size_t kPinBytes = size_t{1} << 18;
+constexpr size_t kPinSegs = 2048;
+// queue dst[0, bytes) = src, both readable by the device until the launch ran
+void queue_copy(mbpt_context *ctx, void *dst, const void *src, size_t bytes);
+// launch what is queued
+int flush_copies(mbpt_context *ctx);
+// device memory dst = host memory src (taken at once) by the next flush_copies
+int queue_upload(mbpt_context *ctx, void *dst, const void *src, size_t bytes);
+// host memory = device memory, for n pieces, waiting for the stream
+struct HostCopy {
+  void *dst;
+  const void *src;
+  size_t bytes;
+};
+int read_back(mbpt_context *ctx, const HostCopy *c, int n);
+// the stream has been waited for: the staging is free again
+inline void stream_done(mbpt_context *ctx) { ctx->pin_used = ctx->pin_segs_used = 0; }
 void gauss_legendre(int n, double *x, double *w);
 int ensure_hf(mbpt_task_set *set);
 int sync_epoch(mbpt_task_set *set);

@@ -342,8 +342,9 @@ size_t stage_bytes_of(const mbpt_server::Compiled &c) {
   return c.bytes + a256(c.dds.size() * sizeof(DiagDev)) + a256(sizeof(TaskDev));
 }
 
-// Returns 0 when admitted, 1 when it does not fit now, < 0 on a HIP error.
-int admit_one(mbpt_server *s, Req &q, int slot) {
+// Returns 0 when admitted, 1 when it does not fit now. Queues the copies of the
+// slot's tables and record; a grid to start from is added to `warm`.
+int admit_one(mbpt_server *s, Req &q, int slot, std::vector<HostCopy> &warm) {
   mbpt_context *ctx = s->ctx;
   const mbpt_server::Compiled &c = compiled_of(s, q.r.order, q.r.diagram_id, q.r.group);
   const size_t gbytes = a256(c.groups.size() * sizeof(GroupDev));
@@ -416,17 +417,11 @@ int admit_one(mbpt_server *s, Req &q, int slot) {
   *sT = T;
   if (slot == 0) s->busy_seen = 0;
   char *b = s->ws;
-  // asynchronous copies from pinned staging: the step's closing
-  // synchronisation orders them before the staging is reused
-  if (need_bytes)
-    MBPT_HIPCHK(ctx, hipMemcpyAsync(b + g_off, st, need_bytes, hipMemcpyHostToDevice, ctx->stream));
-  MBPT_HIPCHK(ctx, hipMemcpyAsync(b + s->L.diags + diag_at * sizeof(DiagDev), sd,
-                                  need_diags * sizeof(DiagDev), hipMemcpyHostToDevice,
-                                  ctx->stream));
-  MBPT_HIPCHK(ctx, hipMemcpyAsync(b + s->L.tasks + slot * sizeof(TaskDev), sT, sizeof(TaskDev),
-                                  hipMemcpyHostToDevice, ctx->stream));
-  KArgs a = server_kargs(s);
-  MBPT_HIPCHK(ctx, launch_init(a, slot, 1, ctx->stream));
+  // copies from pinned staging, launched together for all that a step admits;
+  // its closing synchronisation orders them before the staging is reused
+  queue_copy(ctx, b + g_off, st, need_bytes);
+  queue_copy(ctx, b + s->L.diags + diag_at * sizeof(DiagDev), sd, need_diags * sizeof(DiagDev));
+  queue_copy(ctx, b + s->L.tasks + slot * sizeof(TaskDev), sT, sizeof(TaskDev));
   if (s->warm_dn > 0.0) {
     // nearest retired grid of the same diagram and matter within the window
     int best = -1;
@@ -446,11 +441,11 @@ int admit_one(mbpt_server *s, Req &q, int slot) {
       }
     }
     if (best >= 0) {
+      // (after the launch that sets the admitted slots up)
       const size_t gbytes = static_cast<size_t>(T.nd) * (ctx->desc.n_bins + 1) * sizeof(double);
-      MBPT_HIPCHK(ctx, hipMemcpyAsync(b + s->L.grids + T.grid_off * sizeof(double),
-                                      b + s->L.cache + best * kMaxDim * (ctx->desc.n_bins + 1) *
-                                                           sizeof(double),
-                                      gbytes, hipMemcpyDeviceToDevice, ctx->stream));
+      warm.push_back({b + s->L.grids + T.grid_off * sizeof(double),
+                      b + s->L.cache + best * kMaxDim * (ctx->desc.n_bins + 1) * sizeof(double),
+                      gbytes});
       s->cache[best].stamp = ++s->cache_clock;
       ++s->warm_starts;
     }
@@ -635,6 +630,8 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     return MBPT_ESTATE;
   }
   const bool reg = s->reg_n > 0;
+  std::vector<int> admitted;
+  std::vector<HostCopy> warm;
   while (!s->queue.empty()) {
     int slot = -1;
     for (int i = 0; i < s->max_slots; ++i)
@@ -644,10 +641,22 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
       }
     if (slot < 0) break;
     Req &q = s->reqs[s->queue.front()];
-    const int rc = admit_one(s, q, slot);
-    if (rc == 1) break;  // no room: wait for retirements
-    if (rc < 0) return rc;
+    if (admit_one(s, q, slot, warm)) break;  // no room: wait for retirements
     s->queue.pop_front();
+    admitted.push_back(slot);
+  }
+  if (!admitted.empty()) {
+    // (slots are taken in ascending order: runs of neighbours start together)
+    int rc = flush_copies(ctx);
+    if (rc) return rc;
+    const KArgs a = server_kargs(s);
+    for (size_t i = 0, j; i < admitted.size(); i = j) {
+      for (j = i + 1; j < admitted.size() && admitted[j] == admitted[j - 1] + 1;) ++j;
+      MBPT_HIPCHK(ctx, launch_init(a, admitted[i], static_cast<int>(j - i), ctx->stream));
+    }
+    for (const HostCopy &g : warm) queue_copy(ctx, g.dst, g.src, g.bytes);
+    rc = flush_copies(ctx);
+    if (rc) return rc;
   }
   // plans, and work numbering grouped by order over the resident slots (free
   // slots own none), longest plan first within an order: in iteration j of
@@ -687,13 +696,14 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     order_items(s->h_tasks, active, s->olist, s->ranges);
     std::memcpy(s->pin_tasks, s->h_tasks.data(), s->max_slots * sizeof(TaskDev));
     std::memcpy(s->pin_olist, s->olist.data(), s->olist.size() * sizeof(int2));
-    const size_t width = sizeof(TaskParams);
-    MBPT_HIPCHK(ctx, hipMemcpy2DAsync(s->ws + s->L.tasks, sizeof(TaskDev), s->pin_tasks,
-                                      sizeof(TaskDev), width, s->max_slots, hipMemcpyHostToDevice,
-                                      ctx->stream));
-    MBPT_HIPCHK(ctx, hipMemcpyAsync(s->ws + s->L.olist, s->pin_olist,
-                                    s->olist.size() * sizeof(int2), hipMemcpyHostToDevice,
-                                    ctx->stream));
+    auto *d_tasks = reinterpret_cast<TaskDev *>(s->ws + s->L.tasks);
+    for (int i = 0; i < s->max_slots; ++i)
+      queue_copy(ctx, d_tasks + i, s->pin_tasks + i, sizeof(TaskParams));
+    queue_copy(ctx, s->ws + s->L.olist, s->pin_olist, s->olist.size() * sizeof(int2));
+    {
+      const int rc = flush_copies(ctx);
+      if (rc) return rc;
+    }
     KArgs a = server_kargs(s);
     a.total_items = s->ranges.back().item_end;
     const int prec = ctx->desc.precision;
@@ -712,15 +722,18 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
       MBPT_HIPCHK(ctx, launch_finish(a, 0, s->max_slots, j, ctx->desc.alpha, ctx->stream));
     }
     const TaskDev *st = s->pin_tasks;
-    MBPT_HIPCHK(ctx, hipMemcpyAsync(s->pin_tasks, s->ws + s->L.tasks,
-                                    s->max_slots * sizeof(TaskDev), hipMemcpyDeviceToHost,
-                                    ctx->stream));
+    queue_copy(ctx, s->pin_tasks, d_tasks, s->max_slots * sizeof(TaskDev));
+    {
+      const int rc = flush_copies(ctx);
+      if (rc) return rc;
+    }
     if (reg)
       MBPT_HIPCHK(ctx, hipMemcpyAsync(s->pin_creslog, s->ws + s->L.creslog,
                                       static_cast<size_t>(s->max_slots) * kLogIters * kRegSums *
                                           sizeof(double),
                                       hipMemcpyDeviceToHost, ctx->stream));
     MBPT_HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    stream_done(ctx);
     s->stage_used = 0;
     add_timing(ctx, 1, st[0].t_busy - s->busy_seen);
     s->busy_seen = st[0].t_busy;

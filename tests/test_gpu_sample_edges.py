@@ -84,3 +84,39 @@ def test_refined_grid(M, order, did, nb, alpha):
     pb = O.problem(order, did, density=0.12, seed=1, task_key=5, n_bins=nb, alpha=alpha)
     _, _, _, edges = O.integrate(pb, N, 1)
     assert np.abs(got - np.ravel(edges)).max() < 1e-10
+
+
+@pytest.mark.parametrize("ntasks", [1, 90, 400, 1300])
+def test_staged_copies(M, ntasks):
+    """Parameters, tables and results of sets below and above the staging of the
+    copies: every task's first iteration (a uniform grid: no histogram, whose
+    atomic sums have no fixed order, has entered yet) is the same as alone, the
+    same stream of samples summed in the same order, so equal. Parameters uploaded again and again without a
+    wait go through the staging several times over."""
+    ctx = M.mbpt_context_create(seed=5)
+
+    def integrate(tasks):
+        s = M.mbpt_create_task_set(ctx, tasks)
+        M.mbpt_set_blocking(s, 256, 4)
+        nbytes = M.mbpt_workspace_query(s, 2048, 3)
+        buf, ptr = M.device_workspace(nbytes)
+        M.mbpt_bind_workspace(s, ptr, nbytes, 2048, 3)
+        for k in range(40):
+            M.mbpt_set_training(s, k % 2)
+        M.mbpt_set_density(s, 0.12)
+        per, _ = M.mbpt_integrate(s, 2048, 3)
+        out = []
+        for k, r in enumerate(per):
+            assert r.iters_done == 3 and r.n_evals == 3 * 2048
+            log = M.mbpt_iteration_log(s, k)
+            out.append((log[0][0], log[1][0]))
+        M.mbpt_task_set_destroy(s)
+        del buf
+        return out
+
+    tasks = [(2, 0, M.MBPT_NEUTRON, 0.16, 0.0, k, 0) for k in range(ntasks)]
+    out = integrate(tasks)
+    assert len(set(out)) == ntasks
+    for k in sorted({0, ntasks // 2, ntasks - 1}):
+        assert integrate(tasks[k:k + 1])[0] == out[k]
+    M.mbpt_context_destroy(ctx)
