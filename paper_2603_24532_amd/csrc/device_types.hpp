@@ -62,7 +62,8 @@ struct alignas(16) DiagDev {
 // order 3 and the 39 of order 4 (variant V = diagram id; V = -1 is the
 // generic, descriptor-driven path).  From order 2 on they also hold the
 // label-cycle words per vertex-term choice (cyc_e32, the packing of
-// DiagDev::cyc_e32, plain loop order), and at orders 1-3 the coefficients
+// DiagDev::cyc_e32, plain loop order; checked with the masks, while the
+// kernels' label tables are built from the descriptor's), and at orders 1-3 the coefficients
 // of the neutron-matter label polynomial (label_coef_q2, its one isospin
 // configuration).  The masks are those the generator
 // compiles (loops first, plain loop order); with them the compiler folds the
@@ -143,18 +144,11 @@ struct FixedMasks<3, 2> {
 
 }  // namespace mbpt
 
-// the 39 fourth-order diagrams (generated; per-diagram fourth-order kernels)
+// the 39 fourth-order diagrams (generated; see fixed4)
 #include "fixed_masks_o4.hpp"
 
 namespace mbpt {
 
-// FixedMasks that also hold the diagram's label cycles as compile-time
-// constants (cyc_e32, the packing of DiagDev::cyc_e32): the generated
-// fourth-order tables.
-template <typename F, typename = void>
-struct fixed_cycles : std::false_type {};
-template <typename F>
-struct fixed_cycles<F, std::void_t<decltype(F::cyc_e32)>> : std::true_type {};
 // FixedMasks with the neutron-matter label coefficients (label_coef_q2).
 template <typename F, typename = void>
 struct fixed_labels : std::false_type {};

@@ -1,6 +1,6 @@
 // Writes fixed_masks_o4.hpp: the compile-time descriptor masks and label
 // cycles of the 39 fourth-order diagrams (the generator's, in plain loop
-// order), for the per-diagram fourth-order sample kernels.  Built against the library and run
+// order), for the fourth-order sample kernels.  Built against the library and run
 // from the repository root:
 //
 //   hipcc -std=c++17 -I include -I paper_2603_24532_amd/csrc \

@@ -82,8 +82,8 @@ struct SampleLds {
 
 // Fourth-order nuclear-matter single diagrams with the free spectrum, the
 // quartic regulator and the polynomial label sums: the sample kernels branch
-// per work item to code with the diagram's masks and label cycles as
-// compile-time constants (all 39 diagrams in one kernel, see with_variant).
+// per work item to code with the diagram's masks as compile-time constants
+// (all 39 diagrams in one kernel, see with_variant).
 // One launch covers every diagram, so its last, partly filled round of blocks
 // is paid once per iteration: 39 launches, one per diagram, left the device
 // idle at the end of each.  585 tasks, MI355X: 2^21 samples fp32 34.3 -> 24.8
@@ -755,25 +755,12 @@ __device__ __forceinline__ double group_den(const DiagDev *__restrict__ D, uint3
   return prod;
 }
 
-// True if some vertex-term choice E has every one of its label cycles
-// allowed for at least one isospin (ab: cycles allowed as neutrons or as
-// protons): exactly when some isospin configuration passes the Pauli test.
 // Cycle set and cycle count of E (fourth order and below: at most 17
 // cycles, the 32-bit packing).
-// V: the diagram variant; where FixedMasks<ORDER, V> holds the cycles they
-// are compile-time constants.
 template <int ORDER, int V = -1>
 __device__ __forceinline__ void cycles_of_e(const DiagDev *__restrict__ D, int E,
                                             CycWordV<ORDER, V> &m, uint32_t &n) {
-  if constexpr (ORDER <= 4 && fixed_cycles<FixedMasks<ORDER, V>>::value) {
-    const uint32_t w = FixedMasks<ORDER, V>::cyc_e32[E];
-    m = w & 0xFFFFFFu;
-    n = w >> 24;
-  } else if constexpr (ORDER >= 5 && V == kNarrowCycles) {
-    const uint32_t w = D->cyc_e32[E];
-    m = w & 0xFFFFFFu;
-    n = w >> 24;
-  } else if constexpr (ORDER >= 5) {
+  if constexpr (ORDER >= 5 && V != kNarrowCycles) {
     const uint64_t w = D->cyc_e[E];
     m = w & ((uint64_t{1} << 56) - 1);
     n = static_cast<uint32_t>(w >> 56);
@@ -784,6 +771,9 @@ __device__ __forceinline__ void cycles_of_e(const DiagDev *__restrict__ D, int E
   }
 }
 
+// True if some vertex-term choice E has every one of its label cycles
+// allowed for at least one isospin (ab: cycles allowed as neutrons or as
+// protons): exactly when some isospin configuration passes the Pauli test.
 template <int ORDER, int V = -1>
 __device__ __forceinline__ bool cycle_any(const DiagDev *__restrict__ D, CycWordV<ORDER, V> ab) {
   bool any = false;
@@ -1572,7 +1562,7 @@ __device__ __forceinline__ double eval_sample(const KArgs &a, const TaskDev *__r
 // label sums), where the work after the Pauli test dominates: measured on
 // MI355X, nuclear matter fp32 and fp64 +25% (fp64 persistent +80%), neutron
 // matter fp32 +18% and fp64 +8% (fp64 persistent -10%).  At fourth order it
-// was slower (per-diagram kernels -13%, persistent -10 to -17%).
+// was slower (one diagram a launch -13%, persistent -10 to -17%).
 template <int ORDER, int Q, int P, bool X>
 constexpr bool screen_on() {
   return ORDER >= 5 && (P == 0 || P == 1) && !X;
@@ -2001,7 +1991,6 @@ __device__ __forceinline__ void process_item(const KArgs &a, int t, int item, do
 // within 512 / waves VGPRs, spilling the rest), as measured on MI355X:
 // - fourth order: fp64, fp32, group and regularised kernels run 4-30% faster
 //   at 3 waves (100-200 spilled bytes per thread) than at 2 without spills;
-//   the regularised group kernel gains at 2;
 // - fifth order: fp32, group and explicit-list kernels gain at 3 waves; the
 //   fp64 polynomial kernel (about 360 spilled bytes at 3) and the regularised
 //   single-diagram kernel are faster at their natural occupancy; the
@@ -2011,12 +2000,13 @@ __device__ __forceinline__ void process_item(const KArgs &a, int t, int item, do
 //   fifth-order neutron matter, which loses a third to ~520 spilled bytes.
 // - third order, fp64 and fp32 (single diagrams specialised per diagram):
 //   4 waves with 60-130 spilled bytes beat 3 waves without (4-7%);
-// - nuclear matter with the cycle form of the label sum (single diagrams,
-//   work items of up to 65536 samples): fourth-order fp32 at 4 waves beats 3
-//   by 1-6%; fourth-order fp64, with the loop coefficients from the
-//   descriptor, runs 4% faster at 3 waves than at 4; fourth-order nuclear
-//   group kernels, whose per-member cycle tables leave LDS for 3 blocks per
-//   CU, run 3-5% faster at 3 waves than at 4 and 8-13% faster than at 2;
+// - fourth-order nuclear single diagrams with compile-time masks (fixed4): 3
+//   waves; those that read the descriptor (other regulator exponents):
+//   fp32 at 4 waves beats 3 by 1-6%, fp64 runs 4% faster at 3 than at 4;
+// - fourth-order nuclear group kernels, whose per-member label tables leave
+//   LDS for 3 blocks per CU, run 3-5% faster at 3 waves than at 4 and 8-13%
+//   faster than at 2; the regularised ones spill 304 bytes at 3 (14.2 ms
+//   against 11.9 at 2 for the fourth-order groups at 2^18 samples);
 // - fifth-order nuclear matter with the Pauli screen: fp32 at 3 waves beats 4
 //   by 8% and 2 by 11%, fp64 at 3 beats 2 by 11% and 4 by 16%.
 // Other kernels fit their natural occupancy.

@@ -1,5 +1,5 @@
-// The fourth-order nuclear-matter sample kernel with every diagram's masks and
-// label cycles as compile-time constants (quartic regulator, polynomial label
+// The fourth-order nuclear-matter sample kernel with every diagram's masks
+// as compile-time constants (quartic regulator, polynomial label
 // sums), fp64 (MBPT_FIXED_P 0) or fp32 (1): the build compiles the two in
 // parallel.
 #include "kernels_dev.hpp"

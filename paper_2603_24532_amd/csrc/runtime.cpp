@@ -411,7 +411,7 @@ bool fixed_masks_ok() {
         fixed_labels_match<3, 2>(*get_diagram(3, 2), false);
     r = r && fixed_cycles_match<3, 0>(*get_diagram(3, 0)) &&
         fixed_cycles_match<3, 1>(*get_diagram(3, 1)) && fixed_cycles_match<3, 2>(*get_diagram(3, 2));
-    // the 39 fourth-order diagrams of the per-diagram kernels
+    // the 39 fourth-order diagrams with compile-time masks
     r = r && num_diagrams(4) == 39 &&
         fixed4_match(dev, std::make_integer_sequence<int, 39>{});
     // groups of orders 3 and 4 hold one cycle table per member in LDS
@@ -1393,8 +1393,8 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
     T.nitems = per;
     T.nsamples = samples_per_iter;
   }
-  // within an order, tasks numbered by diagram (the per-diagram kernels take
-  // one diagram's tasks per launch)
+  // within an order, tasks numbered by diagram: neighbouring blocks run the
+  // code of the same diagram
   std::stable_sort(all.begin(), all.end(), [&](int x, int y) {
     return set->diags[set->task_diag[x]].id < set->diags[set->task_diag[y]].id;
   });
