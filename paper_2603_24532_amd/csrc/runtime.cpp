@@ -679,9 +679,18 @@ size_t items_for(const mbpt_task_set *set, uint64_t samples) {
 //   u = 40:  4: 107 / 67, 8: 83 / 54, 16: 85 / 61, 32: 110 / 78
 //   u = 48:  4: 129 / 90, 8: 97 / 67, 16: 88 / 66, 32: 110 / 79
 //   u = 160: 8: 254 / 157, 16: 228 / 149, 32: 226 / 151, 64: 267 / 189
-int launch_spt(uint64_t samples, int block, int cus) {
+// A sample of a diagram group costs its members' sum, and with one block per
+// CU the four wavefronts wait out their own latencies: below u = 12 groups of
+// more than two members take two blocks.  22 members, fp32 / fp64 /
+// regularised:
+//   u = 4:   1: 263 / 168 / 188, 2: 194 / 132 / 158, 4: 270 / 233 / 264
+//   u = 16:  4: 519 / 453 / 556, 8: 479 / 458 / 532, 16: 767 / 815 / 916
+// (of two members 38 / 34 / 43 with 2, 39 / 34 / 43 with 4 at u = 4; of one 33
+// and 30 in fp64)
+int launch_spt(uint64_t samples, int block, int cus, int members) {
   const uint64_t u = samples / (static_cast<uint64_t>(block) * std::max(1, cus));
-  const uint64_t spt = u < 12    ? std::max<uint64_t>(1, std::min<uint64_t>(4, u))
+  const uint64_t per = members > 2 ? 2 : 1;
+  const uint64_t spt = u < 12    ? std::max<uint64_t>(1, std::min<uint64_t>(4, u / per))
                        : u < 44  ? 8
                        : u < 128 ? 16
                        : u < 512 ? 32
@@ -694,6 +703,8 @@ int launch_spt(uint64_t samples, int block, int cus) {
 // tasks of an order otherwise.
 int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
   uint64_t per_launch = max_samples;
+  int members = 1;
+  for (int n : set->task_ndiag) members = std::max(members, n);
   if (set->launch_mode != MBPT_LAUNCH_PER_TASK) {
     int count[kMaxOrder + 1] = {};
     int most = 1;
@@ -701,7 +712,7 @@ int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
       if (t.order >= 1 && t.order <= kMaxOrder) most = std::max(most, ++count[t.order]);
     per_launch = max_samples * static_cast<uint64_t>(most);
   }
-  return launch_spt(per_launch, set->block, set->ctx->num_cus);
+  return launch_spt(per_launch, set->block, set->ctx->num_cus, members);
 }
 
 struct Layout {

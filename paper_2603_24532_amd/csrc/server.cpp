@@ -685,9 +685,14 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
   int spt_of[kMaxOrder + 1];
   {
     uint64_t samples[kMaxOrder + 1] = {};
-    for (int i : active) samples[s->h_tasks[i].order] += s->h_tasks[i].nsamples;
+    int members[kMaxOrder + 1] = {};
+    for (int i : active) {
+      const TaskDev &T = s->h_tasks[i];
+      samples[T.order] += T.nsamples;
+      members[T.order] = std::max(members[T.order], T.ndiag);
+    }
     for (int o = 0; o <= kMaxOrder; ++o)
-      spt_of[o] = std::max(s->spt, launch_spt(samples[o], kBlock, ctx->num_cus));
+      spt_of[o] = std::max(s->spt, launch_spt(samples[o], kBlock, ctx->num_cus, members[o]));
     for (int i : active)
       s->h_tasks[i].nitems = static_cast<int>(
           items_of(s->h_tasks[i].nsamples, spt_of[s->h_tasks[i].order]));
