@@ -32,17 +32,16 @@ sys.path.insert(0, ROOT)
 
 FP64_VECTOR_PEAK_TFLOPS = 78.6    # MI355X published fp64 vector peak
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X published fp32 vector peak (packed fp32 FMA)
-FP32_UNPACKED_PEAK_TFLOPS = 78.6  # 256 CUs x 4 SIMD x 16 lanes x 2 (FMA) x 2.4 GHz, one fp32 op per lane
+# 256 CUs x 4 SIMD x 64 lanes x 2 (FMA) x 2.4 GHz / 2.5 cycles, the measured issue of ordinary fp32 FMAs
+FP32_UNPACKED_PEAK_TFLOPS = 125.8
 
 DENSITIES_PNM = [0.04 + 0.02 * i for i in range(9)]
 DENSITIES_C4 = [0.08, 0.12, 0.16, 0.20, 0.24]
 FRACTIONS_C4 = [0.0, 0.25, 0.5]
 SIGMA_FLOOR = 1e-3  # MeV: absolute sigma floor of the 1% target
 
-# HBM traffic of one headline iteration's sample launches (the 39 per-diagram
-# launches), from two rocprofv3 --pmc runs of `bench.py --workload nuclear4`
-# (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, summed over an iteration's
-# dispatches) scaled by the same counters' reading for a device-to-device copy
+# HBM traffic of one headline iteration's sample launch, from two rocprofv3 --pmc runs of `bench.py --workload nuclear4`
+# (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) scaled by the same counters' reading for a device-to-device copy
 # of known size (--copy-calibration-mib).  Valid only for the kernel sources
 # and work decomposition it was measured with (None: not measured).
 KERNEL_SOURCES = ("paper_2603_24532_amd/csrc/kernels_dev.hpp",
@@ -52,12 +51,13 @@ KERNEL_SOURCES = ("paper_2603_24532_amd/csrc/kernels_dev.hpp",
                   "paper_2603_24532_amd/csrc/device_types.hpp",
                   "paper_2603_24532_amd/csrc/fixed_masks_o4.hpp",
                   "paper_2603_24532_amd/csrc/turn_table.hpp")
-TRAFFIC = {"sha256": "62d0b7c09ded4130c6eb2a38ecfbc58b69f0803efa1f763951120f7ada27c528",
+TRAFFIC = {"sha256": "3c2ef5f58d0ff9933dc165ed64e9a76fe91b9bd113d549ea76a3578becfa49cc",
            "block": 256, "spt": 256,
-           # the 39 sample_order_fixed<4,4,1,2,id> dispatches of an iteration,
-           # summed, mean over the 16 timed iterations of
+           # the sample_order<4,4,1,false,2> dispatch of an iteration, mean over
+           # the 16 timed iterations (4 training, 12 on the frozen grid, which
+           # take no histogram) of
            # `--workload nuclear4 --precision fp32 --steps 16 --warmup 2 --train 4`
-           "fetch_kib": 59086.69, "write_kib": 899755.6,
+           "fetch_kib": 24514.26, "write_kib": 229441.8,
            # 256 MiB device copy: FETCH_SIZE 131083.5 KiB, WRITE_SIZE 262144 KiB
            "fetch_scale": 262144.0 / 131083.5, "write_scale": 1.0}
 
@@ -730,8 +730,8 @@ def headline(args, M, stream):
             "label_sum": "polynomial" if LABEL_MODE == 0 else "explicit",
         },
         "roofline": roofline_of(f32, FP32_VECTOR_PEAK_TFLOPS, {
-            "kernel": "sample_order_fixed<4,4,1,2,id> (fourth order, nuclear matter, fp32 "
-                      "integrand; one launch per diagram id, 39 per iteration, timed together)",
+            "kernel": "sample_order<4,4,1,false,2> (fourth order, nuclear matter, fp32 "
+                      "integrand; all 39 diagrams in one launch per iteration)",
             "threads_per_block": block, "samples_per_thread": spt,
             "traffic": traffic_bytes_per_launch(block, spt),
             "frac_of_unpacked_fp32_peak": None,
