@@ -1998,8 +1998,13 @@ __device__ __forceinline__ void process_item(const KArgs &a, int t, int item, do
 // - HF kernels (isospin-dependent spectra keep per-line energy differences
 //   live): 2 waves from third order on, 20-45% faster than at one, except
 //   fifth-order neutron matter, which loses a third to ~520 spilled bytes.
-// - third order, fp64 and fp32 (single diagrams specialised per diagram):
-//   4 waves with 60-130 spilled bytes beat 3 waves without (4-7%);
+// - third order (single diagrams specialised per diagram), by time per iteration:
+//   4 waves with spilled bytes beat 3 without at large sizes (twelve tasks x
+//   2^21, at 4 / 3 waves: nuclear fp32 371 / 393 us, neutron fp32 355 / 369;
+//   at 5 the fp32 batch of orders 2 and 3 loses 12%); neutron-matter fp64 is
+//   the faster at 3 at every size (2^18 samples 27 / 26 us, 2^23 166 / 160,
+//   twelve tasks x 2^21 425 / 417), nuclear fp64 only at small ones (2^20 45 /
+//   43 us, twelve tasks x 2^21 442 / 453);
 // - fourth-order nuclear single diagrams with compile-time masks (fixed4): 3
 //   waves; those that read the descriptor (other regulator exponents):
 //   fp32 at 4 waves beats 3 by 1-6%, fp64 runs 4% faster at 3 than at 4;
@@ -2022,7 +2027,7 @@ constexpr int min_waves() {
     if (ORDER == 4) return P == 1 ? 4 : 3;
     if (ORDER == 5) return 3;
   }
-  if (ORDER == 3 && (P == 0 || P == 1)) return 4;
+  if (ORDER == 3 && (P == 0 || P == 1)) return Q == 2 && P == 0 ? 3 : 4;
   if (ORDER == 4) return (P == 0 || P == 1 || P == 3 || P == 4 || P == 5) ? 3 : 2;
   if (ORDER == 5) {
     if (P == 1 || P == 3 || P == 4 || (P == 0 && X)) return 3;

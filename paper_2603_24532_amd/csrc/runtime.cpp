@@ -152,7 +152,13 @@ extern "C" int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context *
 extern "C" void mbpt_context_destroy(mbpt_context *ctx) {
   if (!ctx) return;
   // (a copy may still be queued; the caller's stream may be gone already)
-  if (ctx->pin && (ctx->pin_used || ctx->pin_segs_used)) (void)hipDeviceSynchronize();
+  if (ctx->pin && (ctx->pin_used || ctx->pin_segs_used)) {
+    int dev = ctx->desc.device;
+    (void)hipGetDevice(&dev);
+    (void)hipSetDevice(ctx->desc.device);
+    (void)hipDeviceSynchronize();
+    (void)hipSetDevice(dev);
+  }
   if (ctx->pin) (void)hipHostFree(ctx->pin);
   delete ctx;
 }
