@@ -1222,7 +1222,7 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
     // then fits one wave per SIMD instead of two (five nuclear diagrams x 2^23
     // samples, two components, on MI355X: 3.43 ms per iteration, 2.29 this way),
     // and the grouped fourth-order diagrams (15 points x 2^18, three components)
-    // take 10.6 ms instead of 10.3.
+    // take 10.7 ms instead of 10.4.
     const double base = pref * regall * acc * rcp_newton(den);
 #pragma unroll
     for (int r = 0; r < kMaxReg; ++r) {
@@ -1231,7 +1231,8 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
         double x = 1.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) x *= Dn[c] - eta;
-        wr[r] = fma(base, rcp_newton(x), wr[r]);
+        // (a shift may be any finite energy: the product can overflow)
+        wr[r] = fma(base, __builtin_isinf(x) ? 0.0 : rcp_newton(x), wr[r]);
       }
     }
     return base * rcp_newton(dprod);

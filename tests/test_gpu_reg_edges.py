@@ -1,6 +1,8 @@
 """Regularised components where the product over the energy denominators ends:
 first order, which has none (every component is the bare weight), alone, in sets
-of mixed orders and served."""
+of mixed orders and served; and shifts so large that the product of the shifted
+denominators leaves the range of a double (the component goes to zero, the main
+weight is untouched)."""
 import numpy as np
 import pytest
 
@@ -100,3 +102,28 @@ def test_served_first_order(M):
     # of a few per cent: 1e-12 relative is 50 times that
     assert np.allclose(E, r.E_per_A, rtol=1e-12, atol=0), (E, r.E_per_A)
     assert E0 == pytest.approx(r.E_per_A, rel=1e-12)
+
+
+@pytest.mark.parametrize("eta", [1e30, 1e90, 1e300])
+@pytest.mark.parametrize("order,did,q", [(2, 0, 2), (3, 1, 4), (4, 7, 4), (5, 50, 2)])
+def test_large_shift(M, order, did, q, eta):
+    print(f"case reg order={order} q={q} eta={eta}", flush=True)
+    count, x = 1500, 0.3 if q == 4 else 0.0
+    pb = O.problem(order, did, density=0.16, proton_fraction=x, q=q, seed=1, task_key=7,
+                   reg_k=K, reg_eta=eta, label_method=0 if order < 4 or q == 2 else 1)
+    grid = O.uniform_grid(3 * (order + 1))
+    wo, co = O.sample_values(pb, grid, 0, 0, count)
+    wro = O.sample_values_reg(pb, grid, 0, 0, count)
+    run = Run(M, [_task(order, did, q, 0.16, x, 7)], max_samples=4096)
+    try:
+        M.mbpt_set_regularization(run.ctx, K, eta)
+        w = M.mbpt_dump_samples(run.set, 0, 0, 0, count)
+        wr = M.mbpt_dump_samples_reg(run.set, 0, 0, 0, count, K)
+    finally:
+        run.close()
+    _check_samples(w, wo, co, (order, q, eta))
+    # as accurate as w relative to its own size: the factor between them is a
+    # product of denominators, whose condition numbers are in W_cond
+    ratio = np.abs(wro) / np.where(wo != 0, np.abs(wo), np.inf)[:, None]
+    bound = TOL * co[:, None] * ratio + 1e-300
+    assert (np.abs(wr - wro) <= bound).all(), (order, q, eta)
