@@ -1388,7 +1388,8 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   const float y2 = yreg * yhi;
   const float yres = fmaf(yreg, ylo, fmaf(yreg, yhi, -y2));
   const float dall = den * dprod;
-  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || y2 > 115.0f;
+  // (y2 is NaN where p^n overflows a float and Lambda^-n underflows one)
+  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || !(y2 <= 115.0f);
   if (near) {
     fallback = true;
     return 0.0;
