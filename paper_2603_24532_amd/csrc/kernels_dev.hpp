@@ -1286,6 +1286,19 @@ __device__ __forceinline__ double eval_fp64(const KArgs &a, const TaskDev *__res
   return scale * sum;
 }
 
+// Largest product of a diagram's denominators that stays in fp32, its NC energy
+// denominators without hbar^2 / 2m: 1e30 in MeV with nucleons' 20.75 MeV fm^2.
+// Far below the range of a float, and not for its sake alone: beyond it the
+// momenta are large, and the energy denominators of ring diagrams, differences
+// of their squares, lose digits (third-order ring, cutoff 150 fm^-1: error 2.2e-6
+// of W_cond rms, 5.3e-6 with 1e30 fm^-2NC).
+template <int NC>
+constexpr float fp32_den_max() {
+  double m = 1e30;
+  for (int c = 0; c < NC; ++c) m /= 20.75;
+  return static_cast<float>(m);
+}
+
 // Per-sample integrand with fp32 arithmetic after the (fp64) VEGAS map; the
 // Jacobian and the final weight stay fp64.  Sets `fallback` instead of
 // returning a value when the sample lies in the band where fp32 cannot
@@ -1389,7 +1402,8 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   const float yres = fmaf(yreg, ylo, fmaf(yreg, yhi, -y2));
   const float dall = den * dprod;
   // (y2 is NaN where p^n overflows a float and Lambda^-n underflows one)
-  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < 1e30f && den < 1e30f) || !(y2 <= 115.0f);
+  near |= !(fabsf(dall) > 1e-30f && fabsf(dall) < fp32_den_max<NC>() && den < 1e30f) ||
+          !(y2 <= 115.0f);
   if (near) {
     fallback = true;
     return 0.0;
