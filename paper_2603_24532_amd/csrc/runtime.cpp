@@ -107,6 +107,66 @@ void count_flops(const Diagram &d, int q, int half_exp, int label_mode, int spec
 // ---------------------------------------------------------------------------
 // Context
 
+namespace mbpt {
+
+// Pinned staging blocks whose contexts are gone, kept for the next ones: a
+// block takes 15 us to allocate and up to 65 us to free (the runtime waits for
+// its streams).  At most kPinKept of them, free of queued copies; the process's
+// end returns them.
+constexpr size_t kPinKept = 2;
+static std::mutex pin_mu;
+static char *pin_kept[kPinKept];
+static size_t n_pin_kept = 0;
+
+// Allocation and release of pinned memory, allowed while another stream is being
+// captured (they touch no stream; by default any capture in the process would
+// be broken off).
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+void take_pin(mbpt_context *ctx) {
+  if (ctx->pin) return;
+  {
+    std::lock_guard<std::mutex> lock(pin_mu);
+    if (n_pin_kept > 0) {
+      ctx->pin = pin_kept[--n_pin_kept];
+      return;
+    }
+  }
+  const RelaxedCapture relaxed;
+  if (hipHostMalloc(reinterpret_cast<void **>(&ctx->pin), kPinBytes + kPinSegs * sizeof(CopySeg),
+                    hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->pin = nullptr;
+  }
+}
+
+static void give_pin(mbpt_context *ctx) {
+  if (!ctx->pin) return;
+  if (ctx->pin_used || ctx->pin_segs_used) {
+    // a call failed before it waited: copies may still be queued, and the
+    // caller's stream may be gone already
+    int dev = ctx->desc.device;
+    (void)hipGetDevice(&dev);
+    (void)hipSetDevice(ctx->desc.device);
+    (void)hipDeviceSynchronize();
+    (void)hipSetDevice(dev);
+  } else {
+    std::lock_guard<std::mutex> lock(pin_mu);
+    if (n_pin_kept < kPinKept) {
+      pin_kept[n_pin_kept++] = ctx->pin;
+      return;
+    }
+  }
+  const RelaxedCapture relaxed;
+  (void)hipHostFree(ctx->pin);
+}
+
+}  // namespace mbpt
+
 extern "C" int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context **out) {
   if (!out) return MBPT_EINVAL;
   *out = nullptr;
@@ -140,26 +200,13 @@ extern "C" int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context *
   int khz = 0;
   if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, d.device) == hipSuccess && khz > 0)
     ctx->clock_khz = khz;
-  if (hipHostMalloc(reinterpret_cast<void **>(&ctx->pin), kPinBytes + kPinSegs * sizeof(CopySeg),
-                    hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-    (void)hipGetLastError();
-    ctx->pin = nullptr;
-  }
   *out = ctx;
   return MBPT_OK;
 }
 
 extern "C" void mbpt_context_destroy(mbpt_context *ctx) {
   if (!ctx) return;
-  // (a copy may still be queued; the caller's stream may be gone already)
-  if (ctx->pin && (ctx->pin_used || ctx->pin_segs_used)) {
-    int dev = ctx->desc.device;
-    (void)hipGetDevice(&dev);
-    (void)hipSetDevice(ctx->desc.device);
-    (void)hipDeviceSynchronize();
-    (void)hipSetDevice(dev);
-  }
-  if (ctx->pin) (void)hipHostFree(ctx->pin);
+  give_pin(ctx);
   delete ctx;
 }
 
@@ -967,6 +1014,7 @@ int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int 
                      std::to_string(L.total) + ")");
     return MBPT_ENOMEM;
   }
+  take_pin(ctx);
   char *base = static_cast<char *>(ptr);
   set->ws = base;
   set->ws_bytes = bytes;

@@ -45,9 +45,10 @@ struct mbpt_context {
   int reg_n = 0;         // regularised components (0: none)
   double reg_eta = 0.0;  // component k shifts every denominator by -k reg_eta
   double fp32_rel_target = 0.0;  // see mbpt_set_fp32_target
-  // pinned staging: kPinBytes of data and a list of kPinSegs pieces (null: none
-  // could be had, ordinary copies are used instead), the fill of both since the
-  // stream was last waited for, and the pieces queued for the next copy launch
+  // pinned staging: kPinBytes of data and a list of kPinSegs pieces (null: no
+  // set bound yet, or none could be had and ordinary copies are used instead),
+  // the fill of both since the stream was last waited for, and the pieces queued
+  // for the next copy launch
   char *pin = nullptr;
   size_t pin_used = 0, pin_segs_used = 0;
   std::vector<mbpt::CopySeg> segs;
@@ -142,6 +143,8 @@ void add_timing(mbpt_context *ctx, uint64_t launches, uint64_t ticks);
 // the faster, are ordinary copies. Byte counts are multiples of four.
 constexpr size_t kPinBytes = size_t{1} << 18;
 constexpr size_t kPinSegs = 2048;
+// staging for the context, if it has none yet
+void take_pin(mbpt_context *ctx);
 // queue dst[0, bytes) = src, both readable by the device until the launch ran
 void queue_copy(mbpt_context *ctx, void *dst, const void *src, size_t bytes);
 // launch what is queued

@@ -535,6 +535,7 @@ extern "C" int mbpt_server_create(mbpt_context *ctx, int max_slots, uint64_t max
     set_err(ctx, "server_create: workspace too small for the slot table and one request");
     return MBPT_ENOMEM;
   }
+  take_pin(ctx);
   auto *s = new mbpt_server();
   s->ctx = ctx;
   s->max_slots = max_slots;
