@@ -875,7 +875,7 @@ KArgs kargs_of(const mbpt_task_set *set) {
 
 // Precision, interaction or spectrum changed since the set last ran: captured
 // launches, launch shapes and HF tables are stale.
-int upload_params(mbpt_task_set *set);
+int upload_params(mbpt_task_set *set, bool staged = true);
 
 int sync_epoch(mbpt_task_set *set) {
   if (set->epoch == set->ctx->epoch) return MBPT_OK;
@@ -983,21 +983,30 @@ int read_back(mbpt_context *ctx, const HostCopy *c, int n) {
   return MBPT_OK;
 }
 
-// Upload the parameter prefix of every TaskDev (state left untouched).
-int upload_params(mbpt_task_set *set) {
+// Upload the parameter prefix of every TaskDev (state left untouched) and the
+// work list.  staged: through the pinned staging, for callers that wait for the
+// stream.
+int upload_params(mbpt_task_set *set, bool staged) {
   mbpt_context *ctx = set->ctx;
-  const size_t nt = set->h_tasks.size();
+  const size_t nt = set->h_tasks.size(), list = set->olist.size() * sizeof(int2);
   int rc = MBPT_OK;
-  if (ctx->pin && nt * (sizeof(TaskParams) + 64) <= kPinBytes) {
+  if (staged && ctx->pin && nt * (sizeof(TaskParams) + 64) <= kPinBytes) {
     for (size_t t = 0; t < nt && !rc; ++t)
       rc = queue_upload(ctx, set->d_tasks + t, &set->h_tasks[t], sizeof(TaskParams));
   } else {
+    rc = flush_copies(ctx);
+    if (rc) return rc;
     HIPCHK(ctx, hipMemcpy2DAsync(set->d_tasks, sizeof(TaskDev), set->h_tasks.data(),
                                  sizeof(TaskDev), sizeof(TaskParams), nt, hipMemcpyHostToDevice,
                                  ctx->stream));
   }
-  if (!rc)
-    rc = queue_upload(ctx, set->d_olist, set->olist.data(), set->olist.size() * sizeof(int2));
+  if (!staged) {
+    if (list)
+      HIPCHK(ctx, hipMemcpyAsync(set->d_olist, set->olist.data(), list, hipMemcpyHostToDevice,
+                                 ctx->stream));
+    return MBPT_OK;
+  }
+  if (!rc) rc = queue_upload(ctx, set->d_olist, set->olist.data(), list);
   return rc ? rc : flush_copies(ctx);
 }
 
@@ -1280,7 +1289,9 @@ extern "C" int mbpt_set_training(mbpt_task_set *set, int train_iters) {
   for (auto &T : set->h_tasks) T.train_iters = train_iters;
   set->drop_graph();
   if (!set->ws) return MBPT_OK;
-  return upload_params(set);
+  // not staged: the call does not wait, and it may be captured into a caller's
+  // graph, whose replays read the host's parameters of their own time
+  return upload_params(set, false);
 }
 
 extern "C" int mbpt_set_launch_mode(mbpt_task_set *set, int mode) {

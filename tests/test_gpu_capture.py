@@ -71,3 +71,43 @@ def test_contexts_come_and_go(M, mode):
         assert per[0].iters_done == 1 and per[0].n_evals == 1 << 12
     for r in again:
         r.close()
+
+
+def test_training_set_in_a_capture(M):
+    """mbpt_set_training does not wait for the stream, so it may be captured: the
+    graph's replays upload the parameters that the host holds at the time, and a
+    run with replays between its calls (which use the staging of their own copies)
+    gives what the run without them gives."""
+    N = 1 << 13
+
+    def run(replays):
+        r = Run(M, [_task(2, 0, 2, 0.08, 0.0, k) for k in range(3)], max_samples=N, max_iters=16)
+        out = []
+        try:
+            M.mbpt_integrate(r.set, N, 1)
+            if replays:
+                cap = Capture(M, "thread_local", r.stream.cuda_stream)
+                M.mbpt_set_training(r.set, 3)
+                rc, graph = cap.end()
+                assert rc == 0 and graph is not None
+            else:
+                M.mbpt_set_training(r.set, 3)
+            for k in range(4):
+                if k == 2:
+                    M.mbpt_set_density(r.set, 0.1)
+                if replays:
+                    assert cap.hip.hipGraphLaunch(graph, cap.stream) == 0
+                per, _ = M.mbpt_integrate(r.set, N, 2)
+                out.append([(p.iters_done, p.n_evals, p.E_per_A, p.sigma) for p in per])
+            if replays:
+                r.stream.synchronize()
+                cap.hip.hipGraphExecDestroy(graph)
+        finally:
+            r.close()
+        return out
+
+    want, got = run(False), run(True)
+    for a, b in zip(want, got):
+        for x, y in zip(a, b):
+            assert x[:2] == y[:2]
+            assert y[2:] == pytest.approx(x[2:], rel=1e-9)
