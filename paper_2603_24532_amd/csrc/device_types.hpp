@@ -241,6 +241,7 @@ struct alignas(16) TaskParams {
   int train_iters;        // > 0: first train_iters iterations are training (see finish_iteration)
   int active;
   int plan;             // iterations of the current launch sequence it takes part in
+  int spt;              // samples per thread of its work items
 };
 struct alignas(16) TaskState {
   uint32_t iter;        // Philox iteration word of the next iteration
@@ -296,7 +297,6 @@ struct KArgs {
   int pad_reg;
   int ntasks;
   int total_items;
-  int spt;                // samples per thread per item
   int label_mode;         // 0 factorised label sums, 1 explicit terms
   int timed;              // 1: keep the sample-kernel time (TaskState::t_begin, t_busy)
   Phys phys;

@@ -1738,9 +1738,10 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
 
   const uint64_t N = T->nsamples;
   const uint32_t iter = T->iter;
+  const int spt = T->spt;
   const double shift = T->shift;
   const bool hist = adapts(T);
-  const uint64_t base = static_cast<uint64_t>(item - T->item_begin) * bs * a.spt;
+  const uint64_t base = static_cast<uint64_t>(item - T->item_begin) * bs * spt;
   double s1 = 0.0, c1 = 0.0, s2 = 0.0, c2 = 0.0;
   uint32_t npass = 0, nterms = 0, nfb = 0;
   // regularised components: sum (w_k - shift) and sum (w_k - shift)^2 with
@@ -1796,7 +1797,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         }
         wave_queue_pop(pqueue, pn, take, lane);
       };
-      for (int kk = 0; kk < a.spt; ++kk) {
+      for (int kk = 0; kk < spt; ++kk) {
         const uint64_t s = base + static_cast<uint64_t>(kk) * bs + tid;
         bool go = false;
         if (s < N) {
@@ -1810,7 +1811,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
       }
       while (pn > 0) drain_pass(pn < 64 ? pn : 64);
     } else if constexpr (PP != 1) {
-      for (int kk = 0; kk < a.spt; ++kk) {
+      for (int kk = 0; kk < spt; ++kk) {
         const uint64_t s = base + static_cast<uint64_t>(kk) * bs + tid;
         if (s < N) {
           int bins[ND];
@@ -1876,7 +1877,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
           wave_queue_pop(pqueue, pn, take, lane);
           if (qn >= 64) drain(64);
         };
-        for (int kk = 0; kk < a.spt; ++kk) {
+        for (int kk = 0; kk < spt; ++kk) {
           const uint64_t s = base + static_cast<uint64_t>(kk) * bs + tid;
           bool go = false;
           if (s < N) {
@@ -1891,7 +1892,7 @@ __device__ __forceinline__ void item_samples(const KArgs &a, int t, int item, co
         }
         while (pn > 0) drain_pass(pn < 64 ? pn : 64);
       } else {
-        for (int kk = 0; kk < a.spt; ++kk) {
+        for (int kk = 0; kk < spt; ++kk) {
           const uint64_t s = base + static_cast<uint64_t>(kk) * bs + tid;
           bool fb = false;
           if (s < N) {

@@ -866,7 +866,6 @@ KArgs kargs_of(const mbpt_task_set *set) {
   extrapolation_weights(ctx->reg_n, a.reg_coef);
   a.ntasks = static_cast<int>(set->tasks.size());
   a.total_items = 0;
-  a.spt = set->spt;
   a.label_mode = ctx->desc.label_mode;
   a.phys = phys_of(ctx);
   a.phys.spectrum = ctx->desc.spectrum;
@@ -1465,8 +1464,9 @@ extern "C" int mbpt_integrate(mbpt_task_set *set, uint64_t samples_per_iter, int
   for (int t = 0; t < nt; ++t) {
     TaskDev &T = set->h_tasks[t];
     all[t] = t;
-    changed |= T.nitems != per || T.nsamples != samples_per_iter;
+    changed |= T.nitems != per || T.spt != set->spt || T.nsamples != samples_per_iter;
     T.nitems = per;
+    T.spt = set->spt;
     T.nsamples = samples_per_iter;
   }
   // within an order, tasks numbered by diagram: neighbouring blocks run the

@@ -145,6 +145,27 @@ size_t items_of(uint64_t samples, int spt) {
   return static_cast<size_t>((samples + chunk - 1) / chunk);
 }
 
+// Samples per thread of one request's work items, by the request alone, so that
+// its sums are grouped alike whatever else is resident; at least base
+// (server_spt), which its item memory is sized for.  Few large items serve a
+// full server, small ones a request alone, whose iteration lasts as long as an
+// item.  Microseconds for eight iterations on MI355X, one request / 16 / 48 of
+// them, at 2, 4, 8 and 16 samples per thread:
+//   fourth order, 2^16: 234 / 574 / 1241, 260 / 461 / 976, 327 / 454 / 902, 469 / 510 / 886
+//   fourth order, 2^18: 311 / 1555 / 3985, 292 / 1209 / 3119, 340 / 1048 / 2721,
+//                       472 / 1024 / 2557
+//   fifth order, 2^18: 419 / 2733 / 7537, 422 / 2160 / 5908, 544 / 1859 / 4950, 804 / 1818 / 4592
+//   fourth order, 2^20, at 8 and 16: 451 / 3458 / 9924, 504 / 3229 / 9167
+// Groups of more than two members, whose samples cost their sum, keep base (the
+// largest at fourth order, 2^18 samples, alone: 826 at 2, 1261 at 4).
+int request_spt(const mbpt_context *ctx, int base, const mbpt_request &r, size_t members) {
+  if (members > 2) return base;
+  const uint64_t u =
+      r.samples_per_iter / (static_cast<uint64_t>(kBlock) * std::max(1, ctx->num_cus));
+  const int spt = r.order > 4 || u < 4 ? 4 : u < 16 ? 8 : 16;
+  return std::max(base, spt);
+}
+
 size_t per_item_bytes(int nreg) {
   return 4 * sizeof(double) + kItemCounters * sizeof(uint64_t) +
          (nreg > 0 ? kRegSums * sizeof(double) : 0);
@@ -236,7 +257,6 @@ struct mbpt_server {
   int2 *pin_olist = nullptr;
   std::vector<int2> olist;
   std::vector<OrderRange> ranges;
-  std::vector<int> admitted;      // slots admitted in the current step
   // warm starts: grids of recent retirements, one cache entry per slot
   struct CacheEntry {
     bool valid = false;
@@ -281,7 +301,6 @@ KArgs server_kargs(const mbpt_server *s) {
   a.reg_eta = s->reg_eta;
   extrapolation_weights(s->reg_n, a.reg_coef);
   a.ntasks = s->max_slots;
-  a.spt = s->spt;
   a.label_mode = ctx->desc.label_mode;
   a.phys = phys_of(ctx);
   a.phys.spectrum = MBPT_SPECTRUM_FREE;
@@ -351,6 +370,7 @@ int admit_one(mbpt_server *s, Req &q, int slot, std::vector<HostCopy> &warm) {
   const size_t tbytes = a256(c.terms.size() * sizeof(TermDev));
   const size_t need_bytes = c.bytes;
   const size_t need_items = items_of(q.r.samples_per_iter, s->spt);
+  const int spt = request_spt(ctx, s->spt, q.r, c.dds.size());
   const size_t need_diags = c.dds.size();
   const size_t dbytes = a256(need_diags * sizeof(DiagDev));
   // staging: tables (arena image), descriptors, task record
@@ -408,7 +428,8 @@ int admit_one(mbpt_server *s, Req &q, int slot, std::vector<HostCopy> &warm) {
   T.key = static_cast<uint32_t>(q.ticket);
   T.order = q.r.order;
   T.nsamples = q.r.samples_per_iter;
-  T.nitems = static_cast<int>(need_items);
+  T.spt = spt;
+  T.nitems = static_cast<int>(items_of(q.r.samples_per_iter, spt));
   T.store_begin = static_cast<int>(item_at);
   const double x = q.r.matter == MBPT_NUCLEAR ? q.r.proton_fraction : 0.0;
   fill_medium(ctx, q.r.density, x, T);
@@ -680,24 +701,6 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
     return s->h_tasks[x].plan > s->h_tasks[y].plan;
   });
   const int nactive = static_cast<int>(active.size());
-  // samples per thread of each order's launches, from all the samples the first
-  // of them covers; never less than server_spt, which the requests' item
-  // memory is sized for
-  int spt_of[kMaxOrder + 1];
-  {
-    uint64_t samples[kMaxOrder + 1] = {};
-    int members[kMaxOrder + 1] = {};
-    for (int i : active) {
-      const TaskDev &T = s->h_tasks[i];
-      samples[T.order] += T.nsamples;
-      members[T.order] = std::max(members[T.order], T.ndiag);
-    }
-    for (int o = 0; o <= kMaxOrder; ++o)
-      spt_of[o] = std::max(s->spt, launch_spt(samples[o], kBlock, ctx->num_cus, members[o]));
-    for (int i : active)
-      s->h_tasks[i].nitems = static_cast<int>(
-          items_of(s->h_tasks[i].nsamples, spt_of[s->h_tasks[i].order]));
-  }
   if (nactive > 0) {
     order_items(s->h_tasks, active, s->olist, s->ranges);
     std::memcpy(s->pin_tasks, s->h_tasks.data(), s->max_slots * sizeof(TaskDev));
@@ -721,7 +724,6 @@ extern "C" int mbpt_server_step(mbpt_server *s, int *n_active, int *n_queued) {
         while (k1 < r.k1 && s->h_tasks[s->olist[k1].y].plan > j) ++k1;
         if (k1 == r.k0) continue;
         const int end = k1 < r.k1 ? s->olist[k1].x : r.item_end;
-        a.spt = spt_of[r.order];
         MBPT_HIPCHK(ctx, launch_sample_order(a, r.order, 4, prec, r.group, r.k0, k1,
                                              end - s->olist[r.k0].x, kBlock, ctx->stream));
       }
