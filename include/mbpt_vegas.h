@@ -314,11 +314,14 @@ int mbpt_set_training(mbpt_task_set *set, int train_iters);
  * kernels are built for at most 256) and samples per thread per work item
  * (1..256).  EINVAL outside these ranges.  Without this call the block has
  * 256 threads and the samples per thread are chosen at mbpt_bind_workspace
- * for the launch mode the set has then: the larger of a task's samples over
- * about two blocks per CU (at most 16) and one launch's samples (one task in
- * the per-task mode, all tasks of an order otherwise) over about 16 blocks
- * per CU (at most 256).  A later mbpt_set_launch_mode keeps that choice.
- * ESTATE for smaller work items than the bound workspace was sized for. */
+ * from the samples of one launch (one task in the per-task mode, all tasks of
+ * an order otherwise) per thread at one block per CU: up to 4, 8, 16 and 32
+ * with thresholds at 12, 44 and 128, and a sixteenth (at most 256) from 512
+ * on.  A workspace too small for such items but not for a task's samples over
+ * two blocks per CU (at most 16) or a launch's over 16 (at most 256), the
+ * larger of the two, gets that.  A later mbpt_set_launch_mode keeps the choice.
+ * ESTATE for smaller work items than the bound workspace was sized for (the
+ * smaller of the two rules), or than a choice made since. */
 int mbpt_set_blocking(mbpt_task_set *set, int threads_per_block, int samples_per_thread);
 /* The work decomposition in effect (the automatic choice once bound). */
 int mbpt_get_blocking(const mbpt_task_set *set, int *threads_per_block, int *samples_per_thread);
@@ -413,8 +416,8 @@ int mbpt_integrate_batch(mbpt_context *ctx, const mbpt_task_desc *tasks, int n_t
  * each GPU it runs on until the process ends.  Each call starts every task of
  * the set from a uniform grid at iteration 0, runs `iters` iterations on the
  * context stream and returns the results as mbpt_integrate does (same work
- * decomposition as a workspace bound with max_samples_per_iter =
- * samples_per_iter, so the same estimates up to the order of the fp64
+ * decomposition as a workspace of that array's size bound with
+ * max_samples_per_iter = samples_per_iter, so the same estimates up to the order of the fp64
  * histogram atomics); nothing persists in the set, which is left unbound
  * (mbpt_iteration_log, mbpt_get_grid and mbpt_dump_samples still need a
  * bound workspace).  No device memory, event or graph is created: launches

@@ -753,8 +753,16 @@ int launch_spt(uint64_t samples, int block, int cus, int members) {
 
 // Samples per thread unless set explicitly, chosen at bind for the launch mode
 // the set has then: a launch covers one task in the per-task mode, all the
-// tasks of an order otherwise.
-int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
+// tasks of an order otherwise.  spt by launch_spt; alt, the larger of a task's
+// samples over two blocks per CU (at most 16) and a launch's over 16 (at most
+// 256), for its memory: a workspace that holds alt's items only gets alt
+// (slower by up to a fifth, see the table of launch_spt), and where spt's items
+// are the larger ones the workspace still holds alt's, so that
+// mbpt_set_blocking and mbpt_autotune can go down to them.
+struct AutoSpt {
+  int spt, alt;
+};
+AutoSpt auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
   uint64_t per_launch = max_samples;
   int members = 1;
   for (int n : set->task_ndiag) members = std::max(members, n);
@@ -765,7 +773,13 @@ int auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
       if (t.order >= 1 && t.order <= kMaxOrder) most = std::max(most, ++count[t.order]);
     per_launch = max_samples * static_cast<uint64_t>(most);
   }
-  return launch_spt(per_launch, set->block, set->ctx->num_cus, members);
+  const uint64_t per_cu =
+      static_cast<uint64_t>(set->block) * static_cast<uint64_t>(std::max(1, set->ctx->num_cus));
+  const uint64_t task =
+      std::max<uint64_t>(1, std::min<uint64_t>(16, max_samples / (2 * per_cu)));
+  const uint64_t launch = std::min<uint64_t>(256, per_launch / (16 * per_cu));
+  return {launch_spt(per_launch, set->block, set->ctx->num_cus, members),
+          static_cast<int>(std::max(task, launch))};
 }
 
 struct Layout {
@@ -773,10 +787,9 @@ struct Layout {
       gl, cpart, creslog, queue, total;
 };
 
-Layout layout_of(const mbpt_task_set *set, uint64_t max_samples, int max_iters, int nb) {
-  // item capacity for the blocking the set will have once bound
-  const uint64_t chunk = static_cast<uint64_t>(set->block) *
-                         (set->blocking_auto ? auto_spt(set, max_samples) : set->spt);
+// Layout with room for items of `spt` samples per thread.
+Layout layout_of(const mbpt_task_set *set, uint64_t max_samples, int max_iters, int nb, int spt) {
+  const uint64_t chunk = static_cast<uint64_t>(set->block) * spt;
   const size_t items_per_task = static_cast<size_t>((max_samples + chunk - 1) / chunk);
   Layout L{};
   size_t off = 0;
@@ -823,6 +836,23 @@ Layout layout_of(const mbpt_task_set *set, uint64_t max_samples, int max_iters, 
   off = align256(off + kQueueSlots * sizeof(int));
   L.total = off;
   return L;
+}
+
+// Samples per thread of a set bound to `bytes` (0: as many as the query gives),
+// and of the smallest items the layout has room for.
+struct Sizing {
+  int spt, min_spt;
+  Layout L;
+};
+Sizing sizing_of(const mbpt_task_set *set, uint64_t max_samples, int max_iters, size_t bytes) {
+  const int nb = set->ctx->desc.n_bins;
+  if (!set->blocking_auto)
+    return {set->spt, set->spt, layout_of(set, max_samples, max_iters, nb, set->spt)};
+  const AutoSpt a = auto_spt(set, max_samples);
+  const int fine = std::min(a.spt, a.alt), coarse = std::max(a.spt, a.alt);
+  const Layout L = layout_of(set, max_samples, max_iters, nb, fine);
+  if (bytes == 0 || bytes >= L.total) return {a.spt, fine, L};
+  return {coarse, coarse, layout_of(set, max_samples, max_iters, nb, coarse)};
 }
 
 Phys phys_of(const mbpt_context *ctx) {
@@ -1011,12 +1041,12 @@ int upload_params(mbpt_task_set *set, bool staged) {
 
 int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int max_iters) {
   mbpt_context *ctx = set->ctx;
-  const int nb = ctx->desc.n_bins;
   if (!ptr || (reinterpret_cast<uintptr_t>(ptr) & 255u) || max_samples < 2 || max_iters < 1) {
     set_err(ctx, "bind_workspace: null or misaligned pointer, or bad limits");
     return MBPT_EINVAL;
   }
-  const Layout L = layout_of(set, max_samples, max_iters, nb);
+  const Sizing z = sizing_of(set, max_samples, max_iters, bytes);
+  const Layout &L = z.L;
   if (bytes < L.total) {
     set_err(ctx, "bind_workspace: workspace too small (" + std::to_string(bytes) + " < " +
                      std::to_string(L.total) + ")");
@@ -1028,8 +1058,10 @@ int bind(mbpt_task_set *set, void *ptr, size_t bytes, uint64_t max_samples, int 
   set->ws_bytes = bytes;
   set->max_samples = max_samples;
   set->max_iters = max_iters;
-  if (set->blocking_auto) set->spt = auto_spt(set, max_samples);
+  set->spt = z.min_spt;
   set->max_items = set->tasks.size() * items_for(set, max_samples);
+  set->spt = z.spt;
+  set->min_chunk = static_cast<size_t>(set->block) * z.min_spt;
   set->d_tasks = reinterpret_cast<TaskDev *>(base + L.tasks);
   set->d_olist = reinterpret_cast<int2 *>(base + L.olist);
   set->d_diags = reinterpret_cast<DiagDev *>(base + L.diags);
@@ -1313,13 +1345,14 @@ extern "C" int mbpt_set_blocking(mbpt_task_set *set, int threads_per_block, int 
   if (!set || threads_per_block < 64 || threads_per_block > 256 || (threads_per_block % 64) ||
       samples_per_thread < 1 || samples_per_thread > 256)
     return MBPT_EINVAL;
-  if (set->ws && static_cast<size_t>(threads_per_block) * samples_per_thread <
-                     static_cast<size_t>(set->block) * set->spt) {
+  const size_t chunk = static_cast<size_t>(threads_per_block) * samples_per_thread;
+  if (set->ws && chunk < set->min_chunk) {
     set_err(set->ctx, "set_blocking: smaller work items than at bind time need a larger workspace");
     return MBPT_ESTATE;
   }
   set->block = threads_per_block;
   set->spt = samples_per_thread;
+  set->min_chunk = chunk;
   set->blocking_auto = false;
   set->drop_graph();
   set->oranges.clear();
@@ -1329,7 +1362,7 @@ extern "C" int mbpt_set_blocking(mbpt_task_set *set, int threads_per_block, int 
 extern "C" int mbpt_workspace_query(const mbpt_task_set *set, uint64_t max_samples_per_iter,
                                     int max_iters, size_t *bytes) {
   if (!set || !bytes || max_samples_per_iter < 2 || max_iters < 1) return MBPT_EINVAL;
-  *bytes = layout_of(set, max_samples_per_iter, max_iters, set->ctx->desc.n_bins).total;
+  *bytes = sizing_of(set, max_samples_per_iter, max_iters, 0).L.total;
   return MBPT_OK;
 }
 
@@ -1608,7 +1641,7 @@ int integrate_in(mbpt_task_set *set, void *base, size_t bytes, uint64_t samples_
     set_err(ctx, "integrate_noalloc: the set has a workspace bound (use mbpt_integrate)");
     return MBPT_ESTATE;
   }
-  const size_t need = layout_of(set, samples_per_iter, iters, ctx->desc.n_bins).total;
+  const size_t need = sizing_of(set, samples_per_iter, iters, std::max<size_t>(1, bytes)).L.total;
   if (need > bytes) {
     set_err(ctx, "integrate_noalloc: " + std::to_string(set->tasks.size()) + " tasks at " +
                      std::to_string(samples_per_iter) + " samples per iteration and " +
@@ -2059,6 +2092,7 @@ extern "C" int mbpt_autotune(mbpt_task_set *set, uint64_t samples_per_iter, int 
   }
   set->block = best_b;
   set->spt = best_s;
+  set->min_chunk = static_cast<size_t>(best_b) * best_s;
   set->oranges.clear();
   set->drop_graph();
   const int rc = mbpt_reset(set);

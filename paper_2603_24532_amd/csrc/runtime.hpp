@@ -62,6 +62,7 @@ struct mbpt_task_set {
   int launch_mode = MBPT_LAUNCH_PER_TASK;
   int train_iters = 0;  // training/evaluation split (0: off)
   int block = 256, spt = 16;
+  size_t min_chunk = 0;  // samples of the smallest work items that may be asked for (bound)
   bool blocking_auto = true;  // spt chosen at bind from the sample count
   std::vector<mbpt::DiagDev> diags;
   std::vector<mbpt::GroupDev> groups;
