@@ -317,7 +317,9 @@ int mbpt_set_training(mbpt_task_set *set, int train_iters);
  * from the samples of one launch (one task in the per-task mode, all tasks of
  * an order otherwise) per thread at one block per CU: up to 4, 8, 16 and 32
  * with thresholds at 12, 44 and 128, and a sixteenth (at most 256) from 512
- * on.  A workspace too small for such items but not for a task's samples over
+ * on; fewer for costly samples (nuclear matter with explicit label lists from
+ * third order or the HF spectrum from fourth) below 12, and for diagram groups
+ * of more than two members.  A workspace too small for such items but not for a task's samples over
  * two blocks per CU (at most 16) or a launch's over 16 (at most 256), the
  * larger of the two, gets that.  A later mbpt_set_launch_mode keeps the choice.
  * ESTATE for smaller work items than the bound workspace was sized for (the

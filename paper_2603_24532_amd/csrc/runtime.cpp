@@ -732,21 +732,39 @@ size_t items_for(const mbpt_task_set *set, uint64_t samples) {
 //   u = 40:  4: 107 / 67, 8: 83 / 54, 16: 85 / 61, 32: 110 / 78
 //   u = 48:  4: 129 / 90, 8: 97 / 67, 16: 88 / 66, 32: 110 / 79
 //   u = 160: 8: 254 / 157, 16: 228 / 149, 32: 226 / 151, 64: 267 / 189
-// A sample of a diagram group costs its members' sum, and with one block per
-// CU the four wavefronts wait out their own latencies: below u = 12 groups of
-// more than two members take two blocks.  22 members, fp32 / fp64 /
-// regularised:
-//   u = 4:   1: 263 / 168 / 188, 2: 194 / 132 / 158, 4: 270 / 233 / 264
-//   u = 16:  4: 519 / 453 / 556, 8: 479 / 458 / 532, 16: 767 / 815 / 916
-// (of two members 38 / 34 / 43 with 2, 39 / 34 / 43 with 4 at u = 4; of one 33
-// and 30 in fp64)
-int launch_spt(uint64_t samples, int block, int cus, int members) {
+// Samples of ten and more times that cost (heavy: explicit label lists from third
+// order, the HF spectrum from fourth, in nuclear matter) take two blocks per CU
+// below u = 12; at u = 4, by samples per thread:
+//   lists, third order, fp32          2: 56, 4: 61
+//   lists, fourth order, fp64 / fp32  2: 61 / 77, 4: 73 / 96
+//   HF, fourth / fifth order          2: 68 / 98, 4: 81 / 118
+int launch_spt(uint64_t samples, int block, int cus, bool heavy) {
   const uint64_t u = samples / (static_cast<uint64_t>(block) * std::max(1, cus));
-  const uint64_t per = members > 2 ? 2 : 1;
-  const uint64_t spt = u < 12    ? std::max<uint64_t>(1, std::min<uint64_t>(4, u / per))
+  const uint64_t spt = u < 12    ? std::max<uint64_t>(1, std::min<uint64_t>(4, heavy ? u / 2 : u))
                        : u < 44  ? 8
                        : u < 128 ? 16
                        : u < 512 ? 32
+                                 : std::min<uint64_t>(256, u / 16);
+  return static_cast<int>(spt);
+}
+
+// The same for launches that hold diagram groups of more than two members (up
+// to 22), whose samples cost their members' sum: `samples` counts the launch's
+// in units of its largest task's, whose items the launch waits for, and smaller
+// items pay, as their fixed costs are a small part.  Microseconds per iteration
+// of all fourth-order groups in nuclear matter, fp64 / fp32 / regularised:
+//   u = 1.8 (one point, 2^16):   1: 111 / 161 / 127, 2: 151 / 218 / 166, 8: 449 / 515 / 488
+//   u = 7.1 (one, 2^18):         1: 276 / 378 / 372, 2: 228 / 322 / 302, 8: 445 / 516 / 484
+//   u = 27 (15 points, 2^16):    4: 681 / 833 / 886, 8: 704 / 873 / 841, 16: 913 / 1049 / 1008
+//   u = 106 (15, 2^18):          4: 2477 / 3043 / 3358, 8: 2358 / 2703 / 3159,
+//                                16: 2360 / 2642 / 3040, 32: 2623 / 3098 / 3065
+int group_launch_spt(uint64_t samples, int block, int cus) {
+  const uint64_t u = samples / (static_cast<uint64_t>(block) * std::max(1, cus));
+  const uint64_t spt = u < 3     ? 1
+                       : u < 12  ? 2
+                       : u < 40  ? 4
+                       : u < 64  ? 8
+                       : u < 512 ? 16
                                  : std::min<uint64_t>(256, u / 16);
   return static_cast<int>(spt);
 }
@@ -763,22 +781,34 @@ struct AutoSpt {
   int spt, alt;
 };
 AutoSpt auto_spt(const mbpt_task_set *set, uint64_t max_samples) {
-  uint64_t per_launch = max_samples;
-  int members = 1;
-  for (int n : set->task_ndiag) members = std::max(members, n);
-  if (set->launch_mode != MBPT_LAUNCH_PER_TASK) {
-    int count[kMaxOrder + 1] = {};
-    int most = 1;
-    for (const auto &t : set->tasks)
-      if (t.order >= 1 && t.order <= kMaxOrder) most = std::max(most, ++count[t.order]);
-    per_launch = max_samples * static_cast<uint64_t>(most);
+  const mbpt_context *ctx = set->ctx;
+  const bool per_task = set->launch_mode == MBPT_LAUNCH_PER_TASK, nuclear = set->q == 4;
+  uint64_t per_launch = max_samples;  // the largest launch's samples
+  uint64_t weighed = 0;               // with groups, in units of its largest task's
+  bool heavy = false;
+  for (int order = 1; order <= kMaxOrder; ++order) {
+    uint64_t count = 0, members = 0, most = 0;
+    for (size_t t = 0; t < set->tasks.size(); ++t) {
+      if (set->tasks[t].order != order) continue;
+      const uint64_t n = set->task_ndiag[t];
+      count += 1;
+      members += n;
+      most = std::max(most, n);
+    }
+    if (!count) continue;
+    if (!per_task) per_launch = std::max(per_launch, max_samples * count);
+    if (most > 2)
+      weighed = std::max(weighed, per_task ? max_samples : max_samples * members / most);
+    heavy |= nuclear && ((order >= 3 && ctx->desc.label_mode != 0) ||
+                         (order >= 4 && ctx->desc.spectrum != MBPT_SPECTRUM_FREE));
   }
   const uint64_t per_cu =
-      static_cast<uint64_t>(set->block) * static_cast<uint64_t>(std::max(1, set->ctx->num_cus));
+      static_cast<uint64_t>(set->block) * static_cast<uint64_t>(std::max(1, ctx->num_cus));
   const uint64_t task =
       std::max<uint64_t>(1, std::min<uint64_t>(16, max_samples / (2 * per_cu)));
   const uint64_t launch = std::min<uint64_t>(256, per_launch / (16 * per_cu));
-  return {launch_spt(per_launch, set->block, set->ctx->num_cus, members),
+  return {weighed ? group_launch_spt(weighed, set->block, ctx->num_cus)
+                  : launch_spt(per_launch, set->block, ctx->num_cus, heavy),
           static_cast<int>(std::max(task, launch))};
 }
 

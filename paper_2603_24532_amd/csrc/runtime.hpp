@@ -133,7 +133,6 @@ bool poly_fit_at_zero(const double *x, const double *y, const double *sig, int n
                       double &c0, double &s0);
 void extrapolation_weights(int K, double *a);
 bool fixed_masks_ok();
-int launch_spt(uint64_t samples, int block, int cus, int members);
 Phys phys_of(const mbpt_context *ctx);  // all but the spectrum
 void fill_medium(const mbpt_context *ctx, double density, double x, TaskDev &T);
 void result_of(const TaskDev &S, mbpt_result &r);

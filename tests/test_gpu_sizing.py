@@ -117,3 +117,43 @@ def test_larger_sets_than_the_scratch_stay_refused(M):
     finally:
         M.mbpt_task_set_destroy(s)
         M.mbpt_context_destroy(ctx)
+
+
+@pytest.mark.parametrize("points,blocks,most", [(1, 1, 1), (1, 4, 2), (3, 1, 2), (15, 1, 4),
+                                                (3, 4, 4), (1, 16, 4)])
+def test_groups_take_small_items(M, points, blocks, most):
+    """Sets of the four fourth-order groups (3, 22, 13 and 1 members): a launch
+    waits for the items of the largest, so its items are at most a quarter of
+    the launch in units of the largest group's samples (two samples per thread
+    below twelve)."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    samples = 256 * cus * blocks
+    sizes = [len(M.mbpt_group_members(4, p)) for p in range(4)]
+    assert sizes == [3, 22, 13, 1]
+    tasks = [(4, p, 1, 0.16, 0.3, 4 * k + p, 1) for k in range(points) for p in range(4)]
+    ctx, s = _set(M, tasks, mode=1)
+    try:
+        buf = _bind(M, s, M.mbpt_workspace_query(s, samples, 1), samples, 1)
+        assert M.mbpt_get_blocking(s) == (256, most)
+        del buf
+    finally:
+        M.mbpt_task_set_destroy(s)
+        M.mbpt_context_destroy(ctx)
+
+
+@pytest.mark.parametrize("order,did,label_mode,hf", [(3, 1, 1, 0), (4, 20, 1, 0), (4, 20, 0, 1),
+                                                     (5, 300, 0, 1)])
+def test_costly_samples_take_two_blocks_per_cu(M, order, did, label_mode, hf):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    samples = 256 * cus * 4
+    ctx = M.mbpt_context_create(stream=M.current_stream(), label_mode=label_mode, spectrum=hf)
+    s = M.mbpt_create_task_set(ctx, [(order, did, 1, 0.16, 0.3, 1)])
+    try:
+        buf = _bind(M, s, M.mbpt_workspace_query(s, samples, 1), samples, 1)
+        assert M.mbpt_get_blocking(s) == (256, 2)
+        del buf
+    finally:
+        M.mbpt_task_set_destroy(s)
+        M.mbpt_context_destroy(ctx)
