@@ -166,9 +166,9 @@ typedef struct mbpt_server mbpt_server;
 /* ---- context -------------------------------------------------------------- */
 /* Create a context on `device`.  desc may be NULL for defaults (device 0,
  * default stream, FP64, seed 1, 50 bins, alpha 1.5, kcut_extra 3.0, bands
- * 1e-4 / 1e-2, label_mode 0, spectrum FREE).  The default interaction is the synthetic contact + Yukawa one
- * (C0 = -1 fm^2, Cy = -2, mpi = 0.7, Lambda = 2, exponent 4, hbar^2/m = 41.47,
- * hbarc = 197.3269804).  EINVAL on bad fields, EHIP if the device is absent. */
+ * 1e-4 / 1e-2, label_mode 0, spectrum FREE).  The default interaction is the
+ * synthetic contact + Yukawa one (C0 = -1 fm^2, Cy = -2, mpi = 0.7, Lambda = 2,
+ * exponent 4, hbar^2/m = 41.47, hbarc = 197.3269804).  EINVAL on bad fields, EHIP if the device is absent. */
 int mbpt_context_create(const mbpt_context_desc *desc, mbpt_context **out);
 void mbpt_context_destroy(mbpt_context *ctx);
 /* Message of the last failed call on this context (never NULL). */
@@ -450,10 +450,16 @@ int mbpt_set_grid(mbpt_task_set *set, int task, const double *edges_host);
 int mbpt_autotune(mbpt_task_set *set, uint64_t samples_per_iter, int *threads_per_block,
                   int *samples_per_thread, double *ms_per_iter);
 
-/* Timing of the sample kernels since the last call (by the device clock, up
- * to each iteration end): launches,
- * total kernel milliseconds, samples evaluated, and algorithmic FLOPs per evaluation counted from the descriptors (FMA = 2,
- * add/mul = 1, each exp/sqrt/sincos/division = 1). */
+/* Timing of the sample kernels since the last call: launches, total kernel
+ * milliseconds, samples evaluated, and algorithmic FLOPs per evaluation counted
+ * from the descriptors (FMA = 2, add/mul = 1, each exp/sqrt/sincos/division =
+ * 1).  The time is read from the device clock at the iteration ends: per
+ * iteration, from the end of the first task's bookkeeping in the iteration
+ * before (the start of the call's launches in the first) to the start of its
+ * iteration end.  So it includes the gaps between the launches (in the per-task
+ * mode those between its tasks' launches) and iteration ends of other tasks
+ * that outlast the first one's, and leaves out the first task's iteration end,
+ * in the server too. */
 int mbpt_kernel_stats(mbpt_context *ctx, uint64_t *launches, double *kernel_ms,
                       uint64_t *evals, double *flops);
 /* The algorithmic FLOP model behind those figures for one diagram (host only,
@@ -485,9 +491,12 @@ int mbpt_task_flops(const mbpt_task_set *set, int task, double *flops, double *t
  * launch per order present per iteration, one host synchronisation per step),
  * and retires tasks whose sigma reached max(sigma_rel |E|, sigma_abs) (after
  * at least three iterations) or whose evaluations reached max_evals.
- * A request's random stream is keyed by its ticket and its iteration plan by
- * its own state, so its result does not depend on what else is resident
- * (unless warm starts are on, see mbpt_server_set_warm_start).  The server
+ * A request's random stream is keyed by its ticket, its work items by itself
+ * and its iteration plan by its own state, so its result does not depend on
+ * what else is resident (unless warm starts are on, see
+ * mbpt_server_set_warm_start), up to rounding: the histograms' fp64 atomics add
+ * in any order, and single diagrams that run beside a diagram group of their
+ * order take the group kernel's code.  The server
  * takes the free spectrum only (EINVAL / ESTATE with HF).
  *
  * Diagram groups (Sec. III.A; the grouping of mbpt_task_desc.group): a request

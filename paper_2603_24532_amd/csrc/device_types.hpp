@@ -49,10 +49,11 @@ struct alignas(16) DiagDev {
   uint32_t cyc_mask[kMaxCycles];
   uint64_t cyc_e[32];
   uint32_t cyc_e32[32];
-  // The loop coefficients of lmask / pmask_v / qmask_v decoded: sum s < 2 order is line slot s, then (2p, 2p') of each
-  // vertex; fp64, then fp32.  The group kernels, whose member loop runs at
-  // run time, read them through the scalar cache instead of decoding the
-  // masks per sum and sample.
+  // The loop coefficients of lmask / pmask_v / qmask_v decoded: sum s < 2 order
+  // is line slot s, then (2p, 2p') of each vertex; fp64, then fp32.  The
+  // descriptor-driven kernels of orders 4 and 5 and the group kernels, whose
+  // member loop runs at run time, read them through the scalar cache instead of
+  // decoding the masks per sum and sample.
   double coef_d[kDescCoefSums][kDescCoefStride];
   float coef_f[kDescCoefSums][kDescCoefStride];
 };
@@ -60,16 +61,16 @@ struct alignas(16) DiagDev {
 // Compile-time descriptor masks for the diagrams whose kernels are
 // specialised: the one two-body diagram of orders 1 and 2, the three of
 // order 3 and the 39 of order 4 (variant V = diagram id; V = -1 is the
-// generic, descriptor-driven path).  From order 2 on they also hold the
-// label-cycle words per vertex-term choice (cyc_e32, the packing of
-// DiagDev::cyc_e32, plain loop order; checked with the masks, while the
-// kernels' label tables are built from the descriptor's), and at orders 1-3 the coefficients
-// of the neutron-matter label polynomial (label_coef_q2, its one isospin
-// configuration).  The masks are those the generator
-// compiles (loops first, plain loop order); with them the compiler folds the
-// loop-momentum sums, drops the zero coefficients and shares equal vertex
-// momenta.  Task-set and server creation check the generator's masks against
-// these.
+// generic, descriptor-driven path).  At orders 1-3 they also hold the
+// coefficients of the neutron-matter label polynomial (label_coef_q2, its one
+// isospin configuration), and from order 2 on the label-cycle words per
+// vertex-term choice (cyc_e32, the packing of DiagDev::cyc_e32, plain loop
+// order), which no kernel reads: the label tables in LDS are built from the
+// descriptor's, and these check the generator's cycles.  The masks are those
+// the generator compiles (loops first, plain loop order); with them the
+// compiler folds the loop-momentum sums, drops the zero coefficients and shares
+// equal vertex momenta.  Task-set and server creation check the generator's
+// masks and cycles against these.
 template <int ORDER, int V>
 struct FixedMasks {
   static constexpr bool kFixed = false;

@@ -524,11 +524,12 @@ __device__ __forceinline__ void pair_merge(double &s, double &c, double s2, doub
 // r = (f + 1/2) 2^-32, f whole, the mapped coordinate x = e + r w is one fma of
 // f with the pair, scaled to what the loop momentum is built from: the radius
 // R x0, the cosine 2 x1 - 1, and the azimuth in table steps of the turn (AZ),
-// or in turns from -1/2 to 1/2 (fp32: half the rounding of 0 to 1).  Scaling here, once per work item, takes a multiplication per
-// coordinate and the fraction's conversion to [0, 1) out of every sample; on
-// MI355X (with the one-product bin split of vegas_map and the short fp32 root)
-// orders 2+3, 36 tasks x 2^24 fp32, 7.67 -> 6.95 ms per iteration, and the 585
-// fourth-order tasks fp32 (2^21) 24.8 -> 22.9 ms, fp64 (500 009) 7.1 -> 6.6 ms.
+// or in turns from -1/2 to 1/2 (fp32: half the rounding of 0 to 1).  Scaling
+// here, once per work item, takes a multiplication per coordinate and the
+// fraction's conversion to [0, 1) out of every sample; on MI355X (with the
+// one-product bin split of vegas_map and the short fp32 root) orders 2+3, 36
+// tasks x 2^24 fp32, 7.67 -> 6.95 ms per iteration, and the 585 fourth-order
+// tasks fp32 (2^21) 24.8 -> 22.9 ms, fp64 (500 009) 7.1 -> 6.6 ms.
 template <bool AZ>
 __device__ __forceinline__ double2 grid_pair(int m, double e0, double e1, double R) {
   const double w = e1 - e0;
@@ -1067,8 +1068,9 @@ __device__ __forceinline__ double exp_nonpos(double x, const double *ex) {
 // iteration of 2^21 samples on MI355X, orders 2+3 fp32 6.95 -> 6.73 ms).  The
 // regulators come out too, as exp(-yreg), yreg = 4^n sum_v (p^n + p'^n) (n the
 // regulator exponent).  V0, Vy: the interaction, in fp32 divided by
-// Phys::vscale, so that one of them is 1 and the other at most 1.  KY: *ky adds the Yukawa denominators'
-// condition numbers (s + 2 |p.p'|)(1 / dd + 1 / de), if rel (uniform).
+// Phys::vscale, so that one of them is 1 and the other at most 1.  KY: *ky adds
+// the Yukawa denominators' condition numbers (s + 2 |p.p'|)(1 / dd + 1 / de), if
+// rel (uniform).
 template <int ORDER, int V, int HE, bool TD, bool NEG, bool KY, typename F>
 __device__ __forceinline__ void vertex_terms(const KArgs &a, const DiagDev *__restrict__ D,
                                              const F (*k)[3], F V0, F Vy, F *Vd, F *Ve, F &den,
@@ -1125,7 +1127,8 @@ template <int ORDER, int Q, bool HF, bool REG, bool X, int V, int HE, LabelForm 
 __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *__restrict__ T,
                                                 const DiagDev *__restrict__ D,
                                                 const SampleLds &Ls, const double (*k)[3],
-                                                const double *r2, uint32_t &npass, uint32_t &nterms, double *wr) {
+                                                const double *r2, uint32_t &npass,
+                                                uint32_t &nterms, double *wr) {
   constexpr int L = ORDER + 1;
   constexpr int NL = 2 * ORDER;
   constexpr int NC = ORDER - 1;
@@ -1201,8 +1204,8 @@ __device__ __forceinline__ double diag_weight64(const KArgs &a, const TaskDev *_
   }
 
   double Vd[ORDER], Ve[ORDER], den, yreg;
-  vertex_terms<ORDER, V, HE, TD, LF != kConfigs, false, double>(a, D, k, a.phys.V0, a.phys.Vy, Vd, Ve, den,
-                                                    yreg);
+  vertex_terms<ORDER, V, HE, TD, LF != kConfigs, false, double>(a, D, k, a.phys.V0, a.phys.Vy, Vd,
+                                                                Ve, den, yreg);
   const double regall = exp_nonpos(-yreg * (a.phys.invLn * a.phys.quarter_n), Ls.ex);
 
   double acc;
@@ -1392,7 +1395,8 @@ __device__ __forceinline__ double diag_weight32(const KArgs &a, const TaskDev *_
   const float V0 = static_cast<float>(a.phys.V0 / a.phys.vscale);
   const float Vy = static_cast<float>(a.phys.Vy / a.phys.vscale);
   float Vd[ORDER], Ve[ORDER], den, yreg, ky = 0.0f;
-  vertex_terms<ORDER, V, HE, TD, LF != kConfigs, true, float>(a, D, k, V0, Vy, Vd, Ve, den, yreg, rel, &ky);
+  vertex_terms<ORDER, V, HE, TD, LF != kConfigs, true, float>(a, D, k, V0, Vy, Vd, Ve, den, yreg,
+                                                              rel, &ky);
   // regulator exponent in powers of two, yreg times a constant in two parts:
   // one float's rounding of it alone moved every weight the same way (1.3e-7
   // on average at exponents up to 20)
@@ -1489,11 +1493,11 @@ __device__ __forceinline__ double eval_fp32(const KArgs &a, const TaskDev *__res
       if constexpr (group_cycle_form<ORDER, Q, X, false>()) {
         SampleLds Lm = Ls;  // the member's cycle table
         Lm.cyc = static_cast<const char *>(Ls.cyc) + di * cycle_table_bytes<ORDER>();
-        sum += diag_weight32<ORDER, Q, X, V, HE, kCycles, false, TDG>(a, T, D + di, Lm, k, r2, gpass,
-                                                                    gterms, fallback);
+        sum += diag_weight32<ORDER, Q, X, V, HE, kCycles, false, TDG>(a, T, D + di, Lm, k, r2,
+                                                                      gpass, gterms, fallback);
       } else {
-        sum += diag_weight32<ORDER, Q, X, V, HE, kConfigs, false, TDG>(a, T, D + di, Ls, k, r2, gpass,
-                                                                     gterms, fallback);
+        sum += diag_weight32<ORDER, Q, X, V, HE, kConfigs, false, TDG>(a, T, D + di, Ls, k, r2,
+                                                                       gpass, gterms, fallback);
       }
       if (fallback) return 0.0;  // the whole sample is re-evaluated in fp64
     }
@@ -1501,7 +1505,8 @@ __device__ __forceinline__ double eval_fp32(const KArgs &a, const TaskDev *__res
     nterms += gterms;
   } else {
     constexpr LabelForm LF = label_form<ORDER, Q, false, X, false>();
-    sum = diag_weight32<ORDER, Q, X, V, HE, LF, SCR, TD>(a, T, D, Ls, k, r2, npass, nterms, fallback);
+    sum = diag_weight32<ORDER, Q, X, V, HE, LF, SCR, TD>(a, T, D, Ls, k, r2, npass, nterms,
+                                                         fallback);
     if constexpr (SCR) return sum;
     if (fallback) return 0.0;
   }
@@ -1543,14 +1548,16 @@ __device__ __forceinline__ double eval_sample(const KArgs &a, const TaskDev *__r
     constexpr bool AZ = az_steps<P>();
     const double jc = jac_const<ORDER, AZ>(a, T);
     if (PP != 1) {
-      w = eval_fp64<ORDER, Q, PP == 2, G, X, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, PP == 2, G, X, V, false, HE, false, false, AZ>(
+          a, T, D, Ls, jc, s, iter, bins, npass, nterms);
       return;
     }
     bool fb = false;
     w = eval_fp32<ORDER, Q, G, X, V, HE>(a, T, D, Ls, jc, s, iter, bins, npass, nterms, fb);
     if (fb) {
       ++nfb;
-      w = eval_fp64<ORDER, Q, false, G, X, V, false, HE, false, false, AZ>(a, T, D, Ls, jc, s, iter, bins, npass, nterms);
+      w = eval_fp64<ORDER, Q, false, G, X, V, false, HE, false, false, AZ>(
+          a, T, D, Ls, jc, s, iter, bins, npass, nterms);
     }
   });
   return w;
@@ -2068,7 +2075,8 @@ constexpr int persistent_waves() {
 // launch's register allocation that of its own order.  k1 < 0: the items of
 // task k0 alone.
 template <int ORDER, int Q, int P, bool X, int HE>
-__global__ __launch_bounds__(256, (min_waves<ORDER, Q, P, X, HE>())) void sample_order(KArgs a, int k0, int k1) {
+__global__ __launch_bounds__(256, (min_waves<ORDER, Q, P, X, HE>())) void sample_order(
+    KArgs a, int k0, int k1) {
   extern __shared__ double smem[];
   int t = k0, item;
   if (k1 < 0) {
