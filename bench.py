@@ -32,7 +32,8 @@ sys.path.insert(0, ROOT)
 
 FP64_VECTOR_PEAK_TFLOPS = 78.6    # MI355X published fp64 vector peak
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X published fp32 vector peak (packed fp32 FMA)
-# 256 CUs x 4 SIMD x 64 lanes x 2 (FMA) x 2.4 GHz / 2.5 cycles, the measured issue of ordinary fp32 FMAs
+# 256 CUs x 4 SIMD x 64 lanes x 2 (FMA) x 2.4 GHz / 2.5 cycles: unpacked fp32 FMAs of two
+# register operands (profiles/vector_issue_rates.md; of three registers 3.5-4.4 cycles)
 FP32_UNPACKED_PEAK_TFLOPS = 125.8
 
 DENSITIES_PNM = [0.04 + 0.02 * i for i in range(9)]
@@ -40,9 +41,9 @@ DENSITIES_C4 = [0.08, 0.12, 0.16, 0.20, 0.24]
 FRACTIONS_C4 = [0.0, 0.25, 0.5]
 SIGMA_FLOOR = 1e-3  # MeV: absolute sigma floor of the 1% target
 
-# HBM traffic of one headline iteration's sample launch, from two rocprofv3 --pmc runs of `bench.py --workload nuclear4`
-# (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) scaled by the same counters' reading for a device-to-device copy
-# of known size (--copy-calibration-mib).  Valid only for the kernel sources
+# HBM traffic of one headline iteration's sample launch, from two rocprofv3 --pmc runs of
+# `bench.py --workload nuclear4` (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) scaled by the
+# same counters' reading for a device-to-device copy of known size (--copy-calibration-mib).  Valid only for the kernel sources
 # and work decomposition it was measured with (None: not measured).
 KERNEL_SOURCES = ("paper_2603_24532_amd/csrc/kernels_dev.hpp",
                   "paper_2603_24532_amd/csrc/kernels_inst.hip",
@@ -51,13 +52,13 @@ KERNEL_SOURCES = ("paper_2603_24532_amd/csrc/kernels_dev.hpp",
                   "paper_2603_24532_amd/csrc/device_types.hpp",
                   "paper_2603_24532_amd/csrc/fixed_masks_o4.hpp",
                   "paper_2603_24532_amd/csrc/turn_table.hpp")
-TRAFFIC = {"sha256": "d3b397872262a994448e780574b5615722b0cbd6f63ab2dc1b635458e11dc272",
+TRAFFIC = {"sha256": "e7f5c7862657740cc01613b70dd787c847b7cd624f07fc224ea324795d4a01fe",
            "block": 256, "spt": 256,
            # the sample_order<4,4,1,false,2> dispatch of an iteration, mean over
            # the 16 timed iterations (4 training, 12 on the frozen grid, which
            # take no histogram) of
            # `--workload nuclear4 --precision fp32 --steps 16 --warmup 2 --train 4`
-           "fetch_kib": 24516.03, "write_kib": 229664.1,
+           "fetch_kib": 24515.63, "write_kib": 229479.1,
            # 256 MiB device copy: FETCH_SIZE 131083.5 KiB, WRITE_SIZE 262144 KiB
            "fetch_scale": 262144.0 / 131083.5, "write_scale": 1.0}
 
